@@ -255,10 +255,8 @@ __device__ __forceinline__ void haar3(T u[8]) {
 
 // out = (eps Khat + B3 diag(c) B3) v on one box element; sx = eps hy hz / hx,
 // sy = eps hx hz / hy, sz = eps hx hy / hz; c may be skipped (insulator).
-// With kDot, also returns v^T out, taken in the Haar basis before the last
-// transform (H3 is symmetric), so v need not stay live.
-template <typename T, bool kDot = false>
-__device__ __forceinline__ double jv_element(const T v[8], T sx, T sy, T sz, const T c[8], bool have_c, T out[8]) {
+template <typename T>
+__device__ __forceinline__ void jv_element(const T v[8], T sx, T sy, T sz, const T c[8], bool have_c, T out[8]) {
   // Khat diagonal in the Haar basis, times the 1/8 of the final inverse transform
   const T k2 = T(1.0 / 16.0), k6 = T(1.0 / 48.0), k18 = T(1.0 / 144.0);
   T vt[8];
@@ -288,13 +286,7 @@ __device__ __forceinline__ double jv_element(const T v[8], T sx, T sy, T sz, con
 #pragma unroll
     for (int k = 0; k < 8; ++k) out[k] += db[k] * q[k];
   }
-  double d = 0.0;
-  if (kDot) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) d += (double)vt[k] * (double)out[k];
-  }
   haar3(out);
-  return d;
 }
 
 // Interface-charge / Robin sheets as the kernels see them.  Node (a, b) of
@@ -529,6 +521,85 @@ __device__ __forceinline__ double reduce_partials(const double* partial, int n, 
   const volatile double* p = partial;
   for (int i = threadIdx.x; i < n; i += blockDim.x) v += p[i];
   return block_sum(v, sred);
+}
+
+// Sum over the block of one value per thread, the same in every thread
+// (NT = 0: blockDim.x threads, read from the dispatch packet).
+template <int NT = 0>
+__device__ __forceinline__ double block_sum_all(double a, double* sred) {
+  a = wave_sum(a);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 0) sred[wid] = a;
+  __syncthreads();
+  double r = 0.0;
+  const int nw = ((NT ? NT : (int)blockDim.x) + 63) >> 6;
+  for (int w = 0; w < nw; ++w) r += sred[w];
+  return r;
+}
+
+// Sum of n partials (stride, offset) in a fixed order; the result is the
+// same in every thread of the block.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int n, int stride, int off,
+                                               double* sred) {
+  // eight loads in flight per thread before any is added (a load-add loop
+  // would wait for each in turn)
+  double a = 0.0;
+  const int bs = blockDim.x;
+  for (int i0 = threadIdx.x; i0 < n; i0 += 8 * bs) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = (i0 + j * bs < n) ? part[(long)(i0 + j * bs) * stride + off] : 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) a += v[j];
+  }
+  return block_sum_all(a, sred);
+}
+
+// ---- vector kernels ---------------------------------------------------------
+// Four consecutive entries per thread ("chunk"), loaded with 16-byte vector
+// loads when the chunk is whole.  The arrays are 256-byte aligned.
+template <typename T>
+struct Quad {
+  T v[4];
+};
+
+template <typename T>
+__device__ __forceinline__ Quad<T> ld4(const T* __restrict__ a, long c, long N) {
+  Quad<T> q;
+  const long i = 4 * c;
+  if (i + 3 < N) {
+    if constexpr (sizeof(T) == 8) {
+      const double2* p2 = reinterpret_cast<const double2*>(a + i);
+      const double2 u = p2[0], w = p2[1];
+      q.v[0] = u.x; q.v[1] = u.y; q.v[2] = w.x; q.v[3] = w.y;
+    } else {
+      const float4 u = *reinterpret_cast<const float4*>(a + i);
+      q.v[0] = u.x; q.v[1] = u.y; q.v[2] = u.z; q.v[3] = u.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q.v[j] = (i + j < N) ? a[i + j] : T(0);
+  }
+  return q;
+}
+
+template <typename T>
+__device__ __forceinline__ void st4(T* __restrict__ a, long c, long N, const Quad<T>& q) {
+  const long i = 4 * c;
+  if (i + 3 < N) {
+    if constexpr (sizeof(T) == 8) {
+      double2* p2 = reinterpret_cast<double2*>(a + i);
+      p2[0] = make_double2(q.v[0], q.v[1]);
+      p2[1] = make_double2(q.v[2], q.v[3]);
+    } else {
+      *reinterpret_cast<float4*>(a + i) = make_float4(q.v[0], q.v[1], q.v[2], q.v[3]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i + j < N) a[i + j] = q.v[j];
+  }
 }
 
 }  // namespace qe

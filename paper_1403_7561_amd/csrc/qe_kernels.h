@@ -50,24 +50,24 @@ void launch_count(hipStream_t s, int nblocks, const Geom& g, const Charge& ch, c
                   const uint8_t* semi, const double* phi, double* partial, unsigned int* counter, double* out,
                   const Quantum& qm);
 void launch_density(hipStream_t s, int nblocks, const Geom& g, const Charge& ch, const uint8_t* semi,
-                    const double* phi, double* nout, const Quantum& qm);
+                    const double* phi, double* nout, const Quantum& qm, const int* flags = nullptr);
 // Quantum.sbox: per state, the node-index box of its nonzero |psi|^2 (box: [n][6]).
 void launch_state_boxes(hipStream_t s, int nblocks, const Geom& g, const Quantum& qm, int* box);
 // Bits 32 (|psi|^2 not finite or negative) and 64 (phi^(k) not finite) of *flags.
 void launch_validate_quantum(hipStream_t s, int nblocks, const Quantum& qm, int* flags);
-void launch_validate(hipStream_t s, int nblocks, long N, long E, int n_dir, const double* eps, const Doping& dop,
-                     const int32_t* dir_id, const double* phi, int* flags);
-// Coordinates finite and strictly increasing, Dirichlet values finite
-// (flag bits 128 / 256 / 512 for x / y / z, 1024 for the values).
-void launch_validate_mesh(hipStream_t s, int nx, int ny, int nz, const double* x, const double* y, const double* z,
-                          int n_dir, const double* dir_val, int* flags);
-void launch_stage(hipStream_t s, int nblocks, long N, const int32_t* dir_id, const double* dir_val, uint8_t* mask,
-                  double* phi, int apply, int zero_free);
+// Bits of *flags: 1 eps_r, 2 doping, 4 dir_id, 8 phi, 128 / 256 / 512
+// coordinates x / y / z not finite or not strictly increasing, 1024 dir_val.
+void launch_validate(hipStream_t s, int nblocks, const Geom& g, long N, long E, int n_dir, const double* dir_val,
+                     const double* eps, const Doping& dop, const int32_t* dir_id, const double* phi, int* flags);
+// The Dirichlet mask, phi's Dirichlet values (apply) and zeros (zero_free),
+// and the tile-major permittivity of the wave-tiled sweeps (tile_slot).
+void launch_stage(hipStream_t s, int nblocks, const Geom& g, long N, const int32_t* dir_id, const double* dir_val,
+                  uint8_t* mask, double* phi, int apply, int zero_free, const double* eps, double* eps_t, long nslots);
+// The z spacings (as launch_stage_rdz) and zeroed scalars, counters and flags.
+void launch_begin(hipStream_t s, int nz, const double* z, double* rdz, PcgCtx* ctx, unsigned int* counters,
+                  int* flags, double* scal);
 // Inverse z spacings, then the spacings, into g.rdz's buffer (2 (nz - 1) values).
 void launch_stage_rdz(hipStream_t s, int nz, const double* z, double* rdz);
-void launch_cast_d2f(hipStream_t s, int nblocks, long n, const double* a, float* b);
-void launch_masked_copy_d2d(hipStream_t s, int nblocks, long n, const uint8_t* mask, const double* a, double* b);
-void launch_masked_copy_d2f(hipStream_t s, int nblocks, long n, const uint8_t* mask, const double* a, float* b);
 // Coarse-mesh sequence: the coarse problem's coordinates, materials and
 // Dirichlet ids from the fine one (c's arrays are device memory the caller
 // owns), and the coarse potential interpolated onto the fine nodes.
@@ -151,8 +151,7 @@ void launch_cg_jv32(hipStream_t s, const Geom& g, const WaveMap& wm, int cgblock
 // After an FP64 CG loop: the last iteration's x += alpha p (none after a
 // breakdown).
 void launch_cg_finish_x64(hipStream_t s, int nblocks, long N, const PcgCtx* ctx, const double* p, double* x);
-// Tile-major permittivity copy for the wave-tiled J.v (see tile_slot).
-void launch_stage_eps64(hipStream_t s, int nblocks, const Geom& g, const double* eps, double* eps_t, long nslots);
+// FP32 tile-major permittivity for the wave-tiled J.v (see tile_slot).
 void launch_stage_eps32(hipStream_t s, int nblocks, const Geom& g, const double* eps, float* eps_t, long nslots);
 // Count of real elements with a set tile-major flag, added to *out.
 void launch_count_flags(hipStream_t s, int nblocks, const Geom& g, const uint8_t* flag, long nslots,

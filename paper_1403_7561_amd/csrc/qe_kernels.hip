@@ -57,39 +57,6 @@ __device__ __forceinline__ long elem_index(const Geom& g, int ex, int ey, int ez
   return (long)ex + (long)(g.nx - 1) * ((long)ey + (long)(g.ny - 1) * ez);
 }
 
-// Sum over the block of one value per thread, the same in every thread
-// (NT = 0: blockDim.x threads, read from the dispatch packet).
-template <int NT = 0>
-__device__ __forceinline__ double block_sum_all(double a, double* sred) {
-  a = wave_sum(a);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sred[wid] = a;
-  __syncthreads();
-  double r = 0.0;
-  const int nw = ((NT ? NT : (int)blockDim.x) + 63) >> 6;
-  for (int w = 0; w < nw; ++w) r += sred[w];
-  return r;
-}
-
-// Sum of n partials (stride, offset) in a fixed order; the result is the
-// same in every thread of the block.
-__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int n, int stride, int off,
-                                               double* sred) {
-  // eight loads in flight per thread before any is added (a load-add loop
-  // would wait for each in turn)
-  double a = 0.0;
-  const int bs = blockDim.x;
-  for (int i0 = threadIdx.x; i0 < n; i0 += 8 * bs) {
-    double v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = (i0 + j * bs < n) ? part[(long)(i0 + j * bs) * stride + off] : 0.0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) a += v[j];
-  }
-  return block_sum_all(a, sred);
-}
-
 // ---------------------------------------------------------------------------
 // Wave-tiled kernels: four independent waves per block, one wave tile each
 // (see qe_tiles.h).  No LDS and no block barrier in the sweep, so memory
@@ -238,7 +205,7 @@ __device__ __forceinline__ void residual_wave(
   }
   const WaveTile w(g, wx, wy, wz, wm.kz, threadIdx.x & 63, active);
   double acc = 0.0;
-  residual_tile<TD, kQ>(g, w, ch, eps, semi, dop, mask, phi, delta, lam, fsheet, fdiag, F, invdiag, diag_out, cq, cq32,
+  residual_tile<kQ>(g, w, ch, eps, semi, dop, mask, phi, TrialStep<TD>{delta, lam}, fsheet, fdiag, F, invdiag, diag_out, cq, cq32,
                         cflag, (active && cbits) ? cbits + 64L * wid + (threadIdx.x & 63) : nullptr, invdiag32,
                         acc, &qm);
   const double d = wave_sum(acc);
@@ -542,10 +509,12 @@ __global__ __launch_bounds__(kVecThreads) void k_count(
   }
 }
 
-// Nodal density: n(phi_i) if node i touches a semiconductor element, else 0.
+// Nodal density: n(phi_i) if node i touches a semiconductor element, else 0
+// (nothing is written when *flags says that the inputs were invalid).
 __global__ __launch_bounds__(kVecThreads) void k_density(Geom g, Charge ch, const uint8_t* __restrict__ semi,
                                                         const double* __restrict__ phi, double* __restrict__ nout,
-                                                        Quantum qm) {
+                                                        Quantum qm, const int* __restrict__ flags) {
+  if (flags && *flags != 0) return;
   const long N = (long)g.nx * g.ny * g.nz;
   for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x) {
     const int i = (int)(n % g.nx);
@@ -586,51 +555,65 @@ __global__ __launch_bounds__(kVecThreads) void k_density(Geom g, Charge ch, cons
 // ---------------------------------------------------------------------------
 // Input validation.  Sets bits of *flags: 1 eps not finite/positive,
 // 2 net doping not finite or a dopant density not finite and >= 0,
-// 4 dir_id out of range, 8 phi not finite.
-__global__ __launch_bounds__(kVecThreads) void k_validate(long N, long E, int n_dir, const double* __restrict__ eps,
-                                                         const Doping dop, const int32_t* __restrict__ dir_id,
+// 4 dir_id out of range, 8 phi not finite, 128 / 256 / 512 x / y / z has a
+// value that is not finite or not above the one before it, 1024 a Dirichlet
+// value is not finite.
+__global__ __launch_bounds__(kVecThreads) void k_validate(Geom g, long N, long E, int n_dir,
+                                                         const double* __restrict__ dir_val,
+                                                         const double* __restrict__ eps, const Doping dop,
+                                                         const int32_t* __restrict__ dir_id,
                                                          const double* __restrict__ phi, int* flags) {
+  const long t0 = (long)blockIdx.x * blockDim.x + threadIdx.x, stride = (long)gridDim.x * blockDim.x;
   int f = 0;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += (long)gridDim.x * blockDim.x) {
+  for (long e = t0; e < E; e += stride) {
     const double v = eps[e];
     if (!(v > 0.0) || !isfinite(v)) f |= 1;
     if (dop.net && !isfinite(dop.net[e])) f |= 2;
     if (dop.donors && !(dop.donors[e] >= 0.0 && isfinite(dop.donors[e]))) f |= 2;
     if (dop.acceptors && !(dop.acceptors[e] >= 0.0 && isfinite(dop.acceptors[e]))) f |= 2;
   }
-  for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x) {
+  for (long n = t0; n < N; n += stride) {
     const int d = dir_id[n];
     if (d < -1 || d >= n_dir) f |= 4;
     if (phi && !isfinite(phi[n])) f |= 8;
   }
-  if (f) atomicOr(flags, f);
-}
-
-// Mesh coordinates and Dirichlet values: bits 128 / 256 / 512 of *flags when
-// x / y / z has a value that is not finite or not above the one before it,
-// 1024 when a Dirichlet value is not finite.
-__global__ __launch_bounds__(kVecThreads) void k_validate_mesh(int nx, int ny, int nz, const double* __restrict__ x,
-                                                              const double* __restrict__ y,
-                                                              const double* __restrict__ z, int n_dir,
-                                                              const double* __restrict__ dir_val, int* flags) {
-  const int n[3] = {nx, ny, nz};
-  const double* c[3] = {x, y, z};
-  int f = 0;
+  const int n[3] = {g.nx, g.ny, g.nz};
+  const double* c[3] = {g.x, g.y, g.z};
+#pragma unroll
   for (int a = 0; a < 3; ++a)
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n[a]; i += gridDim.x * blockDim.x) {
+    for (long i = t0; i < n[a]; i += stride) {
       const double v = c[a][i];
       if (!isfinite(v) || (i > 0 && !(v > c[a][i - 1]))) f |= 128 << a;
     }
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_dir; i += gridDim.x * blockDim.x)
+  for (long i = t0; i < n_dir; i += stride)
     if (!isfinite(dir_val[i])) f |= 1024;
   if (f) atomicOr(flags, f);
 }
 
+// Tile-major copy of the per-element permittivity (padding slots 0).
+template <typename T>
+__device__ __forceinline__ void stage_eps_tiles(const Geom& g, const double* __restrict__ eps, T* __restrict__ eps_t,
+                                                long nslots) {
+  const int gx = (g.nx + 6) / 7, gy = (g.ny + 6) / 7;
+  for (long sl = (long)blockIdx.x * blockDim.x + threadIdx.x; sl < nslots; sl += (long)gridDim.x * blockDim.x) {
+    const int j = (int)(sl % 49);
+    const long blk = sl / 49;
+    const int tx = (int)(blk % gx), ty = (int)((blk / gx) % gy), L = (int)(blk / ((long)gx * gy));
+    const int ex = 7 * tx + j % 7, ey = 7 * ty + j / 7;
+    T v = T(0);
+    if (ex < g.nx - 1 && ey < g.ny - 1 && L < g.nz - 1) v = (T)eps[elem_index(g, ex, ey, L)];
+    eps_t[sl] = v;
+  }
+}
+
 // mask[i] = node i is Dirichlet.  Optionally sets phi on Dirichlet nodes to
-// its value and (zero_free) free nodes to 0.
-__global__ __launch_bounds__(kVecThreads) void k_stage(long N, const int32_t* __restrict__ dir_id,
+// its value and (zero_free) free nodes to 0.  Then the tile-major copy of the
+// per-element permittivity (padding slots 0).
+__global__ __launch_bounds__(kVecThreads) void k_stage(Geom g, long N, const int32_t* __restrict__ dir_id,
                                                       const double* __restrict__ dir_val, uint8_t* __restrict__ mask,
-                                                      double* __restrict__ phi, int apply, int zero_free) {
+                                                      double* __restrict__ phi, int apply, int zero_free,
+                                                      const double* __restrict__ eps, double* __restrict__ eps_t,
+                                                      long nslots) {
   for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x) {
     const int d = dir_id[n];
     mask[n] = d >= 0 ? 1 : 0;
@@ -641,6 +624,7 @@ __global__ __launch_bounds__(kVecThreads) void k_stage(long N, const int32_t* __
         phi[n] = 0.0;
     }
   }
+  stage_eps_tiles(g, eps, eps_t, nslots);
 }
 
 // Inverse z spacings 1 / (z[k+1] - z[k]) for the element stiffness weights,
@@ -654,34 +638,27 @@ __global__ __launch_bounds__(kVecThreads) void k_stage_rdz(int nz, const double*
   }
 }
 
-template <typename TS, typename TD>
-__global__ __launch_bounds__(kVecThreads) void k_cast(long n, const TS* __restrict__ a, TD* __restrict__ b) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    b[i] = (TD)a[i];
+// The first launch of a call: the z spacings, and the device scalars,
+// reduction counters and validation flags zeroed (memory sets cost a launch
+// each, and a captured graph may not hold them).
+__global__ __launch_bounds__(kVecThreads) void k_begin(int nz, const double* __restrict__ z, double* __restrict__ rdz,
+                                                      PcgCtx* __restrict__ ctx, unsigned int* __restrict__ counters,
+                                                      int* __restrict__ flags, double* __restrict__ scal) {
+  for (int k = (int)threadIdx.x; k < nz - 1; k += kVecThreads) {
+    const double h = z[k + 1] - z[k];
+    rdz[k] = 1.0 / h;
+    rdz[nz - 1 + k] = h;
+  }
+  if (threadIdx.x < sizeof(PcgCtx) / 4) reinterpret_cast<unsigned int*>(ctx)[threadIdx.x] = 0u;
+  if (threadIdx.x < 16) counters[threadIdx.x] = 0u;
+  if (threadIdx.x < 4) flags[threadIdx.x] = 0;
+  if (threadIdx.x < 64) scal[threadIdx.x] = 0.0;
 }
 
-// b = a with Dirichlet entries zeroed (converted to TD)
-template <typename TS, typename TD>
-__global__ __launch_bounds__(kVecThreads) void k_masked_copy(long n, const uint8_t* __restrict__ mask,
-                                                            const TS* __restrict__ a, TD* __restrict__ b) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    b[i] = mask[i] ? TD(0) : (TD)a[i];
-}
-
-// Tile-major copy of the per-element permittivity (padding slots 0).
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_stage_eps(Geom g, const double* __restrict__ eps,
                                                           T* __restrict__ eps_t, long nslots) {
-  const int gx = (g.nx + 6) / 7, gy = (g.ny + 6) / 7;
-  for (long sl = (long)blockIdx.x * blockDim.x + threadIdx.x; sl < nslots; sl += (long)gridDim.x * blockDim.x) {
-    const int j = (int)(sl % 49);
-    const long blk = sl / 49;
-    const int tx = (int)(blk % gx), ty = (int)((blk / gx) % gy), L = (int)(blk / ((long)gx * gy));
-    const int ex = 7 * tx + j % 7, ey = 7 * ty + j / 7;
-    T v = T(0);
-    if (ex < g.nx - 1 && ey < g.ny - 1 && L < g.nz - 1) v = (T)eps[elem_index(g, ex, ey, L)];
-    eps_t[sl] = v;
-  }
+  stage_eps_tiles(g, eps, eps_t, nslots);
 }
 
 // Number of real elements whose tile-major flag is set (padding slots of
@@ -718,51 +695,6 @@ __global__ __launch_bounds__(kVecThreads) void k_axpy_phi(long N, double* __rest
 // r^T z in ctx->rzs[k & 1]; the host passes the parity of k with every launch
 // (chunks of iterations have even length, so a captured chunk can be replayed),
 // and block 0 of the direction kernel counts the iterations.
-
-// Four consecutive entries per thread ("chunk"), loaded with 16-byte vector
-// loads when the chunk is whole.  The arrays are 256-byte aligned.
-template <typename T>
-struct Quad {
-  T v[4];
-};
-
-template <typename T>
-__device__ __forceinline__ Quad<T> ld4(const T* __restrict__ a, long c, long N) {
-  Quad<T> q;
-  const long i = 4 * c;
-  if (i + 3 < N) {
-    if constexpr (sizeof(T) == 8) {
-      const double2* p2 = reinterpret_cast<const double2*>(a + i);
-      const double2 u = p2[0], w = p2[1];
-      q.v[0] = u.x; q.v[1] = u.y; q.v[2] = w.x; q.v[3] = w.y;
-    } else {
-      const float4 u = *reinterpret_cast<const float4*>(a + i);
-      q.v[0] = u.x; q.v[1] = u.y; q.v[2] = u.z; q.v[3] = u.w;
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) q.v[j] = (i + j < N) ? a[i + j] : T(0);
-  }
-  return q;
-}
-
-template <typename T>
-__device__ __forceinline__ void st4(T* __restrict__ a, long c, long N, const Quad<T>& q) {
-  const long i = 4 * c;
-  if (i + 3 < N) {
-    if constexpr (sizeof(T) == 8) {
-      double2* p2 = reinterpret_cast<double2*>(a + i);
-      p2[0] = make_double2(q.v[0], q.v[1]);
-      p2[1] = make_double2(q.v[2], q.v[3]);
-    } else {
-      *reinterpret_cast<float4*>(a + i) = make_float4(q.v[0], q.v[1], q.v[2], q.v[3]);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (i + j < N) a[i + j] = q.v[j];
-  }
-}
 
 // x = 0, r = sign*b on free nodes, z = D^-1 r; partials of r^T z.
 template <typename T, typename TB>
@@ -947,8 +879,8 @@ void launch_count(hipStream_t s, int nblocks, const Geom& g, const Charge& ch, c
 }
 
 void launch_density(hipStream_t s, int nblocks, const Geom& g, const Charge& ch, const uint8_t* semi,
-                    const double* phi, double* nout, const Quantum& qm) {
-  QE_LAUNCH(k_density, nblocks, kVecThreads, s, g, ch, semi, phi, nout, qm);
+                    const double* phi, double* nout, const Quantum& qm, const int* flags) {
+  QE_LAUNCH(k_density, nblocks, kVecThreads, s, g, ch, semi, phi, nout, qm, flags);
 }
 
 __global__ __launch_bounds__(kVecThreads) void k_validate_quantum(Quantum qm, int* flags) {
@@ -1047,37 +979,23 @@ void launch_validate_quantum(hipStream_t s, int nblocks, const Quantum& qm, int*
   QE_LAUNCH(k_validate_quantum, nblocks, kVecThreads, s, qm, flags);
 }
 
-void launch_validate(hipStream_t s, int nblocks, long N, long E, int n_dir, const double* eps, const Doping& dop,
-                     const int32_t* dir_id, const double* phi, int* flags) {
-  QE_LAUNCH(k_validate, nblocks, kVecThreads, s, N, E, n_dir, eps, dop, dir_id, phi, flags);
+void launch_validate(hipStream_t s, int nblocks, const Geom& g, long N, long E, int n_dir, const double* dir_val,
+                     const double* eps, const Doping& dop, const int32_t* dir_id, const double* phi, int* flags) {
+  QE_LAUNCH(k_validate, nblocks, kVecThreads, s, g, N, E, n_dir, dir_val, eps, dop, dir_id, phi, flags);
 }
 
-void launch_validate_mesh(hipStream_t s, int nx, int ny, int nz, const double* x, const double* y, const double* z,
-                          int n_dir, const double* dir_val, int* flags) {
-  const int longest = std::max(std::max(nx, ny), std::max(nz, n_dir));
-  QE_LAUNCH(k_validate_mesh, std::max(1, std::min((longest + kVecThreads - 1) / kVecThreads, 64)), kVecThreads, s, nx,
-            ny, nz, x, y, z, n_dir, dir_val, flags);
+void launch_stage(hipStream_t s, int nblocks, const Geom& g, long N, const int32_t* dir_id, const double* dir_val,
+                  uint8_t* mask, double* phi, int apply, int zero_free, const double* eps, double* eps_t, long nslots) {
+  QE_LAUNCH(k_stage, nblocks, kVecThreads, s, g, N, dir_id, dir_val, mask, phi, apply, zero_free, eps, eps_t, nslots);
 }
 
-void launch_stage(hipStream_t s, int nblocks, long N, const int32_t* dir_id, const double* dir_val, uint8_t* mask,
-                  double* phi, int apply, int zero_free) {
-  QE_LAUNCH(k_stage, nblocks, kVecThreads, s, N, dir_id, dir_val, mask, phi, apply, zero_free);
+void launch_begin(hipStream_t s, int nz, const double* z, double* rdz, PcgCtx* ctx, unsigned int* counters,
+                  int* flags, double* scal) {
+  QE_LAUNCH(k_begin, 1, kVecThreads, s, nz, z, rdz, ctx, counters, flags, scal);
 }
 
 void launch_stage_rdz(hipStream_t s, int nz, const double* z, double* rdz) {
   QE_LAUNCH(k_stage_rdz, 1, kVecThreads, s, nz, z, rdz);
-}
-
-void launch_cast_d2f(hipStream_t s, int nblocks, long n, const double* a, float* b) {
-  QE_LAUNCH((k_cast<double, float>), nblocks, kVecThreads, s, n, a, b);
-}
-
-void launch_masked_copy_d2d(hipStream_t s, int nblocks, long n, const uint8_t* mask, const double* a, double* b) {
-  QE_LAUNCH((k_masked_copy<double, double>), nblocks, kVecThreads, s, n, mask, a, b);
-}
-
-void launch_masked_copy_d2f(hipStream_t s, int nblocks, long n, const uint8_t* mask, const double* a, float* b) {
-  QE_LAUNCH((k_masked_copy<double, float>), nblocks, kVecThreads, s, n, mask, a, b);
 }
 
 // J.v lanes' coefficient flags from the owners' element flags: bit L - Lbeg
@@ -1143,10 +1061,6 @@ void launch_cg_jv32(hipStream_t s, const Geom& g, const WaveMap& wm, int cgblock
                     PcgCtx* ctx, CgProgress* prog, const double* part_rz, double* part_py) {
   QE_LAUNCH(k_cg_jv<float>, wm.nblocks, 256, s, g, wm, eps_t, cbits, cq, z, y, p, x, k, ctx, prog, part_rz, cgblocks,
             part_py);
-}
-
-void launch_stage_eps64(hipStream_t s, int nblocks, const Geom& g, const double* eps, double* eps_t, long nslots) {
-  QE_LAUNCH(k_stage_eps<double>, nblocks, kVecThreads, s, g, eps, eps_t, nslots);
 }
 
 void launch_stage_eps32(hipStream_t s, int nblocks, const Geom& g, const double* eps, float* eps_t, long nslots) {

@@ -498,7 +498,7 @@ __global__ __launch_bounds__(kVecThreads) void k_mg_l1(Geom g, const double* __r
             c[m] = cq[8 * sl + m];
             ones[m] = 1.0;
           }
-          jv_element<double, false>(ones, 0.0, 0.0, 0.0, c, true, out);
+          jv_element<double>(ones, 0.0, 0.0, 0.0, c, true, out);
           const int li = (1 - (q & 1)) + 2 * (1 - (q >> 1));
           bot += out[li];
           top += out[li + 4];

@@ -29,7 +29,20 @@
 
 namespace qe {
 
-struct HostMirror;
+// Host memory for scalar read-backs (one per thread): pinned, with a
+// host-coherent word the CG's stopping kernel posts to; or, for the entry
+// point that allocates nothing, the thread's own static storage (no posted
+// word: that CG loop is polled by stream synchronisations).
+struct HostMirror {
+  PcgCtx* ctx = nullptr;
+  double* scal = nullptr;
+  int* flags = nullptr;
+  volatile CgProgress* prog = nullptr;   // host-coherent: written by the device while it runs
+  CgProgress* prog_dev = nullptr;        // the same memory as the device addresses it
+  bool ok = false;
+};
+HostMirror& mirror();
+constexpr int kEventRing = 8;
 qe_status fail(qe_status st, const char* fmt, ...);
 void clear_error();
 qe_status make_charge(const qe_physics* ph, Charge& ch);
@@ -63,6 +76,7 @@ struct MgRun {
 };
 
 // One call's view of a problem, its workspace and its stream.
+struct MarchArgs;
 struct Context {
   qe_problem prob;
   Geom g;
@@ -71,7 +85,6 @@ struct Context {
   WaveMap wmq;   // the residual with eigenstates (wm without them)
   SheetSet sheets{};
   Quantum quantum{};
-  static constexpr int kEventRing = 8;
   hipEvent_t events[kEventRing] = {};   // CG progress markers, created on first use
   ~Context() {
     for (hipEvent_t e : events)
@@ -95,10 +108,14 @@ struct Context {
   // library's choice for the mesh)
   qe_status init(const qe_problem* p, const Charge& ch, void* ws, size_t ws_bytes, void* stream, int kz = 0,
                  bool no_alloc = false, int wave_kz = 0);
+  MarchArgs march_args(const Charge& ch, const qe_options* o, double* phi, double newton_rtol);
   Doping doping() const;
   // Device-side checks of the problem's arrays (coordinates, Dirichlet ids
   // and values, eps_r, doping, sheets, states) and of phi: one round trip.
   qe_status validate(const double* phi);
+  // The same checks queued without waiting, and an error for their flags.
+  void queue_validate(const double* phi);
+  static qe_status flag_error(int f);
   qe_status stage(double* phi, int apply, int zero_free);
   qe_status residual(const Charge& ch, const double* phi, const double* d64, const float* d32, double lam, bool mixed,
                      double* diag_out, double* norm2_host);

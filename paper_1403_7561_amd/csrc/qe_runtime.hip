@@ -18,6 +18,7 @@
 
 #include "../../include/qe.h"
 #include "qe_kernels.h"
+#include "qe_march.h"
 #include "qe_runtime.h"
 
 namespace qe {
@@ -401,19 +402,6 @@ qe_status check_options(const qe_options* o) {
   return QE_OK;
 }
 
-// Host memory for scalar read-backs (one per thread): pinned, with a
-// host-coherent word the CG's stopping kernel posts to; or, for the entry
-// point that allocates nothing, the thread's own static storage (no posted
-// word: that CG loop is polled by stream synchronisations).
-struct HostMirror {
-  PcgCtx* ctx = nullptr;
-  double* scal = nullptr;
-  int* flags = nullptr;
-  volatile CgProgress* prog = nullptr;   // host-coherent: written by the device while it runs
-  CgProgress* prog_dev = nullptr;        // the same memory as the device addresses it
-  bool ok = false;
-};
-
 static HostMirror make_pinned_mirror() {
   HostMirror m;
   void* a = nullptr;
@@ -483,7 +471,8 @@ qe_status Context::init(const qe_problem* p, const Charge& ch, void* ws_, size_t
   if (!hm->ok) return fail(QE_ERR_HIP, "pinned host buffer allocation failed");
   g.rdz = f64(lay.rdz);
   g.hz = g.rdz + (p->nz - 1);
-  launch_stage_rdz(s, p->nz, p->z, f64(lay.rdz));
+  launch_begin(s, p->nz, p->z, f64(lay.rdz), reinterpret_cast<PcgCtx*>(ws + lay.ctx),
+               reinterpret_cast<unsigned int*>(ws + lay.counters), reinterpret_cast<int*>(ws + lay.flags), f64(lay.scal));
   std::vector<int4> items;
   sheets = make_sheets(p, items);
   if (sheets.n > 0) {
@@ -496,10 +485,7 @@ qe_status Context::init(const qe_problem* p, const Charge& ch, void* ws_, size_t
     quantum.sbox = reinterpret_cast<const int*>(ws + lay.sbox);
     launch_state_boxes(s, vblocks, g, quantum, reinterpret_cast<int*>(ws + lay.sbox));
   }
-  // reset device scalars and reduction counters
-  QE_HIP(hipMemsetAsync(ws + lay.ctx, 0, sizeof(PcgCtx), s));
-  QE_HIP(hipMemsetAsync(ws + lay.counters, 0, 16 * sizeof(unsigned int), s));
-  QE_HIP(hipMemsetAsync(ws + lay.flags, 0, 16, s));
+  QE_HIP(hipGetLastError());
   return QE_OK;
 }
 
@@ -510,16 +496,23 @@ Doping Context::doping() const {
 
 // Device-side checks of the coordinates, Dirichlet ids and values, eps_r,
 // doping, sheets, states and (optionally) phi.
-qe_status Context::validate(const double* phi) {
+void Context::queue_validate(const double* phi) {
   int* dflags = reinterpret_cast<int*>(ws + lay.flags);
-  launch_validate_mesh(s, prob.nx, prob.ny, prob.nz, prob.x, prob.y, prob.z, prob.n_dir, prob.dir_val, dflags);
-  launch_validate(s, vblocks, N, E, prob.n_dir, prob.eps_r, doping(), prob.dir_id, phi, dflags);
+  launch_validate(s, vblocks, g, N, E, prob.n_dir, prob.dir_val, prob.eps_r, doping(), prob.dir_id, phi, dflags);
   if (sheets.n > 0) launch_validate_sheets(s, sheets, dflags);
   if (quantum.n > 0) launch_validate_quantum(s, vblocks, quantum, dflags);
+}
+
+qe_status Context::validate(const double* phi) {
+  queue_validate(phi);
   QE_HIP(hipGetLastError());
+  const int* dflags = reinterpret_cast<const int*>(ws + lay.flags);
   QE_HIP(hipMemcpyAsync(hm->flags, dflags, sizeof(int), hipMemcpyDeviceToHost, s));
   QE_HIP(hipStreamSynchronize(s));
-  const int f = *hm->flags;
+  return flag_error(*hm->flags);
+}
+
+qe_status Context::flag_error(int f) {
   for (int a = 0; a < 3; ++a)
     if (f & (128 << a)) return fail(QE_ERR_INVALID_ARG, "coordinates %c not finite or not strictly increasing", "xyz"[a]);
   if (f & 1024) return fail(QE_ERR_NONFINITE, "dir_val not finite");
@@ -534,8 +527,8 @@ qe_status Context::validate(const double* phi) {
 }
 
 qe_status Context::stage(double* phi, int apply, int zero_free) {
-  launch_stage(s, vblocks, N, prob.dir_id, prob.dir_val, u8(lay.mask), phi, apply, zero_free);
-  launch_stage_eps64(s, vblocks, g, prob.eps_r, f64(lay.eps_t), nslots);
+  launch_stage(s, vblocks, g, N, prob.dir_id, prob.dir_val, u8(lay.mask), phi, apply, zero_free, prob.eps_r,
+               f64(lay.eps_t), nslots);
   QE_HIP(hipGetLastError());
   return QE_OK;
 }
@@ -555,6 +548,61 @@ qe_status Context::residual(const Charge& ch, const double* phi, const double* d
     *norm2_host = hm->scal[0];
   }
   return QE_OK;
+}
+
+#ifndef QE_CG_EVENT_EVERY
+#define QE_CG_EVENT_EVERY 8
+#endif
+// This call's problem and work arrays as a march of one instance (F shares
+// r's array: the march needs only one of them at a time).
+MarchArgs Context::march_args(const Charge& ch, const qe_options* o, double* phi, double newton_rtol) {
+  MarchArgs a;
+  std::memset(&a, 0, sizeof(a));
+  MarchInst& I = a.one;
+  I.g = g;
+  I.wm = wm;
+  I.eps = prob.eps_r;
+  I.semi = prob.semi;
+  I.dop = doping();
+  I.dir_id = prob.dir_id;
+  I.dir_val = prob.dir_val;
+  I.phi = phi;
+  I.x = f64(lay.x);
+  I.r = f64(lay.r);
+  I.z = f64(lay.z);
+  I.p = f64(lay.p);
+  I.y = f64(lay.y);
+  I.invdiag = f64(lay.invdiag);
+  I.c = f64(lay.c);
+  I.eps_t = f64(lay.eps_t);
+  I.rdz = f64(lay.rdz);
+  I.mask = u8(lay.mask);
+  I.cflag = u8(lay.cflag);
+  I.cbits = u32(lay.cbits);
+  I.part_a = f64(lay.partial);
+  I.part_b = f64(lay.partial2);
+  static_assert(2 * sizeof(MarchState) <= 512, "the states share the scalar block");
+  I.sa = reinterpret_cast<MarchState*>(ws + lay.scal);
+  I.sb = I.sa + 1;
+  I.N = N;
+  I.E = E;
+  I.nslots = nslots;
+  I.na = wm.nblocks;
+  I.nb = march_blocks_b(N);
+  I.n_dir = prob.n_dir;
+  a.n_inst = 1;
+  a.na = I.na;
+  a.nb = I.nb;
+  a.ch = ch;
+  a.atol = o->newton_atol;
+  a.rtol_max = o->krylov_rtol_max;
+  a.newton_rtol = newton_rtol;
+  a.newton_maxit = o->newton_maxit;
+  a.ls_max = o->ls_max_halvings;
+  a.krylov_maxit = o->krylov_maxit;
+  a.flags = reinterpret_cast<int*>(ws + lay.flags);
+  a.done = u32(lay.counters) + 8;
+  return a;
 }
 
 // Jacobi-PCG on J x = sign*b (free rows).  Returns the CG status through
@@ -601,9 +649,6 @@ qe_status Context::pcg(bool mixed, const double* b, double sign, double rtol, in
   // memory only when it stops the solve (convergence, non-finite values, the
   // iteration limit in iteration maxit; the second kernel on breakdown), once
   // per solve; the queued iterations after that return at once.
-#ifndef QE_CG_EVENT_EVERY
-#define QE_CG_EVENT_EVERY 8
-#endif
   constexpr int kRing = kEventRing;
   // a multigrid iteration (~25 launches) outlasts the host's reaction to an
   // event several times over: an event after each, two iterations ahead
@@ -706,6 +751,49 @@ qe_status Context::pcg_polled(bool mixed, const double* b, double sign, double r
         QE_HIP(hipGetLastError());
       }
       return QE_OK;
+    }
+  }
+}
+
+// The march's host loop: ticks are queued ahead of the device, with an event
+// after every kEv-th, until the kernel that finishes the last instance posts
+// the word; without the posted word (the entry point that allocates nothing)
+// the stream is synchronised and the count read after every 16 ticks.  The
+// ticks queued after the end return at once.
+qe_status march_run(hipStream_t s, MarchArgs& a, HostMirror& hm, hipEvent_t* ring, int ahead) {
+  a.prog = hm.prog_dev;
+  if (!hm.prog_dev) {
+    for (;;) {
+      for (int t = 0; t < 16; ++t) launch_march_tick(s, a);
+      QE_HIP(hipGetLastError());
+      QE_HIP(hipMemcpyAsync(hm.flags, a.done, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
+      QE_HIP(hipStreamSynchronize(s));
+      if (*reinterpret_cast<unsigned int*>(hm.flags) >= (unsigned int)a.n_inst) return QE_OK;
+    }
+  }
+  constexpr int kEv = QE_CG_EVENT_EVERY;
+  for (int e = 0; e < kEventRing; ++e)
+    if (!ring[e]) QE_HIP(hipEventCreateWithFlags(&ring[e], hipEventDisableTiming));
+  ahead = std::min(std::max(ahead > 0 ? ahead : kEv + 1, kEv + 1), kEv * (kEventRing - 1));
+  long queued = 0, finished = 0, head = 0, tail = 0;   // events [head, tail) pending, in ring order
+  for (;;) {
+    while (queued < finished + ahead) {
+      launch_march_tick(s, a);
+      if (++queued % kEv == 0) {
+        QE_HIP(hipEventRecord(ring[tail % kEventRing], s));
+        ++tail;
+      }
+    }
+    QE_HIP(hipGetLastError());
+    if (hm.prog->word) return QE_OK;
+    if (head < tail) {
+      const hipError_t e = hipEventQuery(ring[head % kEventRing]);
+      if (e == hipSuccess) {
+        ++head;
+        finished = head * kEv;
+      } else if (e != hipErrorNotReady) {
+        return fail(QE_ERR_HIP, "solve stream failed: %s", hipGetErrorString(e));
+      }
     }
   }
 }
@@ -1156,28 +1244,38 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
   Context cx;
   if ((st = cx.init(p, ch, ws, ws_bytes, stream, 0, no_alloc)) != QE_OK) return finish(st, r, rep);
   const bool mixed = o->precision == QE_PREC_MIXED;
+  MgState mg;
+  mg.plan_for(p, o, ws, ws_bytes, mixed, no_alloc);
+  // FP64 with Jacobi alone marches on the device; the host drives the solves
+  // with multigrid, sheets or eigenstates and the FP32 CG
+  const bool march = !mixed && !mg.possible && cx.sheets.n == 0 && cx.quantum.n == 0;
+  SeqPlan sp;
+  const size_t fine = align256(fine_layout_bytes(p));
+  char* base = reinterpret_cast<char*>(ws) + fine;
+  const int levels = seq_levels < 0 ? seq_levels_wanted() : seq_levels;
+  const bool seq = o->init_guess == 2 && ws_bytes >= fine && seq_plan(p, base, sp, levels) && ws_bytes - fine >= sp.total;
   // (trusted: a coarse problem built here from a checked one needs no
-  // checks, each a round trip to the device)
-  if (!trusted && (st = cx.validate(o->init_guess == 1 ? phi : nullptr)) != QE_OK) return finish(st, r, rep);
+  // checks, each a round trip to the device; a march from this mesh's own
+  // start checks on the device and reports with its result)
+  const bool march_checks = march && !trusted && !seq;
+  if (!trusted && !march_checks && (st = cx.validate(o->init_guess == 1 ? phi : nullptr)) != QE_OK)
+    return finish(st, r, rep);
   // coarse-mesh sequence: the coarse problem's arrays are built from this
   // one's (validated above), solved, and its potential interpolated into phi
   bool linear = o->init_guess == 0;
   if (o->init_guess == 2) {
-    SeqPlan sp;
-    const size_t fine = align256(fine_layout_bytes(p));
-    char* base = reinterpret_cast<char*>(ws) + fine;
-    const int levels = seq_levels < 0 ? seq_levels_wanted() : seq_levels;
-    if (ws_bytes >= fine && seq_plan(p, base, sp, levels) && ws_bytes - fine >= sp.total) {
+    if (seq) {
       launch_seq_coarsen(cx.s, p, &sp.pc);
       if (hipGetLastError() != hipSuccess) return finish(fail(QE_ERR_HIP, "coarsening launch failed"), r, rep);
       qe_report rc;
       double* phic = reinterpret_cast<double*>(base + sp.o_phi);
-      // the coarse solve only starts this one: its CG runs in FP32 (inside
-      // its FP64 Newton), as in mixed precision (the 129x129x65 solve's
-      // step: 9.46-9.57 -> 9.20-9.43 ms, the same iteration counts, phi equal
-      // to 1e-15)
+      // the coarse solve only starts this one: on meshes that multigrid may
+      // serve its CG runs in FP32 (inside its FP64 Newton), as in mixed
+      // precision; below them it marches in FP64, which costs less than the
+      // host round trips of the FP32 CG's Newton
       qe_options oc = *o;
-      oc.precision = QE_PREC_MIXED;
+      MgPlan coarse_mg;
+      oc.precision = mg_plan(&sp.pc, base, coarse_mg) ? QE_PREC_MIXED : QE_PREC_FP64;
       const qe_status sc = solve_impl(&sp.pc, ph, &oc, phic, nullptr, base + sp.o_ws, sp.total - sp.o_ws, stream, &rc,
                                       no_alloc, seq_rtol((long)sp.pc.nx * sp.pc.ny * sp.pc.nz), levels - 1, true);
       if (sc == QE_ERR_HIP) return finish(sc, r, rep);
@@ -1192,6 +1290,57 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
     }
     linear = r.seq_levels == 0;
   }
+  if (march) {
+    MarchArgs a = cx.march_args(ch, o, phi, newton_rtol);
+    a.init = linear ? MARCH_LINEAR : MARCH_INITIAL;
+    a.apply = 1;
+    a.zero_free = linear ? 1 : 0;
+    const int* flags = march_checks ? a.flags : nullptr;
+    if (march_checks) cx.queue_validate(o->init_guess == 1 ? phi : nullptr);
+    HostMirror& hm = *cx.hm;
+    MarchState& S = *reinterpret_cast<MarchState*>(hm.scal);
+    // the state (and with it the validation flags) of the instance, after the
+    // density at the solution
+    auto result = [&]() {
+      if (n_nodal) launch_density(cx.s, cx.vblocks, cx.g, ch, p->semi, phi, n_nodal, cx.quantum, flags);
+      return hipMemcpyAsync(&S, a.one.sb, sizeof(S), hipMemcpyDeviceToHost, cx.s) == hipSuccess &&
+             hipStreamSynchronize(cx.s) == hipSuccess && hipGetLastError() == hipSuccess;
+    };
+    a.flags = const_cast<int*>(flags);
+    if (hm.prog) hm.prog->word = 0;
+    a.prog = hm.prog_dev;
+    launch_march_stage(cx.s, a);
+    if ((st = march_run(cx.s, a, hm, cx.events, o->check_every)) != QE_OK) return finish(st, r, rep);
+    if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
+    if (S.flags) return finish(Context::flag_error(S.flags), r, rep);
+    if (linear) r.init_krylov_iters = S.init_kry;
+    r.krylov_iters += S.kry;
+    r.newton_iters = S.newton;
+    r.ls_halvings = S.halv;
+    r.n_residual_evals = S.nres;
+    r.res0 = S.res0;
+    r.res_final = S.nrm;
+    const char* cg = "";
+    switch (S.status) {
+      case QE_ERR_NOT_CONVERGED:
+        st = fail(QE_ERR_NOT_CONVERGED, "Newton did not reach atol %.3e in %d steps (||F|| = %.3e)", o->newton_atol,
+                  o->newton_maxit, S.nrm);
+        break;
+      case QE_ERR_LINESEARCH:
+        st = fail(QE_ERR_LINESEARCH, "line search failed at Newton step %d (||F|| = %.3e)", S.newton, S.nrm);
+        break;
+      case QE_ERR_NONFINITE:
+      case QE_ERR_KRYLOV_BREAKDOWN:
+        cg = S.stage == MARCH_LINEAR ? "linear initial guess" : S.stage == MARCH_INITIAL ? "initial guess" : "Newton step";
+        st = S.stage == MARCH_NEWTON || S.why > PCG_CONVERGED
+                 ? fail((qe_status)S.status, "%s %d: CG failed (status %d)", cg, S.newton, S.why)
+                 : fail((qe_status)S.status, "residual not finite at the %s", cg);
+        break;
+      default:
+        st = (qe_status)S.status;
+    }
+    return finish(st, r, rep);
+  }
   if ((st = cx.stage(phi, 1, linear ? 1 : 0)) != QE_OK) return finish(st, r, rep);
   if (mixed) {
     launch_stage_eps32(cx.s, cx.vblocks, cx.g, p->eps_r, cx.f32(cx.lay.eps32), cx.nslots);
@@ -1199,8 +1348,6 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
   }
   const int check = o->check_every;
   int pst = 0, its = 0;
-  MgState mg;
-  mg.plan_for(p, o, ws, ws_bytes, mixed, no_alloc);
   if (linear) {
     // charge-free linear Poisson with the doping kept: one Newton step from
     // phi = (Dirichlet values, 0) on the linear problem

@@ -1,5 +1,5 @@
-// Wave-level element tiles shared by the single-instance kernels and the
-// batched persistent kernel.
+// Wave-level element tiles shared by the residual, J.v, CG and eigensolver
+// kernels.
 //
 // A wave owns an 8 x 8 column of elements -- lane (lx, ly) = element
 // (7 wx - 1 + lx, 7 wy - 1 + ly) -- and the 7 x 7 node columns that are the
@@ -141,15 +141,11 @@ struct WaveTile {
 // coefficient adds exactly nothing).  Modes:
 //   JV_PLAIN  y = J v with v read as 0 on Dirichlet nodes; identity_rows
 //             (1: y = v on Dirichlet rows, 2: y = 0 there).
-//   JV_DOT    v = a CG direction (zero on Dirichlet nodes); y = J v on every
-//             owned row; dot += v^T J v over the elements this wave owns.
 //   JV_SMOOTH as JV_PLAIN with identity_rows = 2, then a smoothing step:
 //             y = v + S (b - J v) on every owned node (S is 0 on Dirichlet
 //             nodes), y a buffer other than v; dot += b^T y over them.
-// In the CG mode the Dirichlet flag is not read at all: the vectors vanish
-// on Dirichlet nodes and D^-1 is 0 there, so whatever y holds on those rows
-// never reaches z, p or x.  (The single-instance CG uses jv_tile_cg below.)
-enum JvMode { JV_PLAIN = 0, JV_DOT = 1, JV_SMOOTH = 2 };
+// (The CG uses jv_tile_cg below.)
+enum JvMode { JV_PLAIN = 0, JV_SMOOTH = 2 };
 
 // cbits: this lane's coefficient flags over the chunk (bit L - Lbeg), as
 // written by residual_tile for the same wave tile.
@@ -159,7 +155,6 @@ __device__ __forceinline__ void jv_tile(const Geom& g, const WaveTile& w, const 
                                         const uint8_t* __restrict__ mask, const T* __restrict__ v,
                                         T* __restrict__ y, int identity_rows, double& dot,
                                         const T* __restrict__ sm_b = nullptr, const T* __restrict__ sm_S = nullptr) {
-  constexpr bool kPlain = kMode != JV_DOT;
   constexpr bool kSmooth = kMode == JV_SMOOTH;
   const unsigned int sbits = cbits;
   auto face = [&](int P, T f[4]) {
@@ -168,7 +163,7 @@ __device__ __forceinline__ void jv_tile(const Geom& g, const WaveTile& w, const 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       T val = v[b + o[k]];
-      if (kPlain && mask[b + o[k]]) val = T(0);
+      if (mask[b + o[k]]) val = T(0);
       f[k] = val;
     }
   };
@@ -191,7 +186,7 @@ __device__ __forceinline__ void jv_tile(const Geom& g, const WaveTile& w, const 
     ee = eps_t[sl];
     if (sbits & 1u) load8(cq + 8 * sl, cc);
   }
-  if (kPlain && w.node_ok && w.Lbeg >= 0) mk = mask[w.node(g, w.Lbeg)];
+  if (w.node_ok && w.Lbeg >= 0) mk = mask[w.node(g, w.Lbeg)];
   // the chunk's z spacings: lane j holds layer Lbeg + j, read per layer with
   // readlane (scalar, no memory access in the sweep)
   double zlo = 0.0, zhi = 1.0, rdzl = 1.0;
@@ -232,7 +227,7 @@ __device__ __forceinline__ void jv_tile(const Geom& g, const WaveTile& w, const 
       en = eps_t[sl];
       if ((sbits >> (L1 - w.Lbeg)) & 1u) load8(cq + 8 * sl, cn);
     }
-    if (kPlain && w.node_ok && L1 <= w.Lend) mkn = mask[w.node(g, L1)];
+    if (w.node_ok && L1 <= w.Lend) mkn = mask[w.node(g, L1)];
     if (kSmooth && w.node_ok && L1 <= w.Lend) {
       const long n1 = w.node(g, L1);
       xsn = v[n1];
@@ -243,9 +238,7 @@ __device__ __forceinline__ void jv_tile(const Geom& g, const WaveTile& w, const 
     if (w.col_ok && layer_ok) {
       const T sx = ee * T(ahx * hz), sy = ee * T(ahy * hz), sz = ee * T(axy * rhz);
       const T ve[8] = {fb[0], fb[1], fb[2], fb[3], ft[0], ft[1], ft[2], ft[3]};
-      const double d =
-          jv_element<T, kMode == JV_DOT>(ve, sx, sy, sz, cc, ((sbits >> (L - w.Lbeg)) & 1u) != 0, out);
-      if (kMode == JV_DOT && w.own_el && L >= w.k0) dot += d;
+      jv_element(ve, sx, sy, sz, cc, ((sbits >> (L - w.Lbeg)) & 1u) != 0, out);
     } else {
 #pragma unroll
       for (int k = 0; k < 8; ++k) out[k] = T(0);
@@ -255,7 +248,7 @@ __device__ __forceinline__ void jv_tile(const Geom& g, const WaveTile& w, const 
     if (w.node_ok && L >= w.k0) {
       const long n = w.node(g, L);
       T val = carry + bot;
-      if (kPlain && mk && identity_rows) val = identity_rows == 1 ? v[n] : T(0);
+      if (mk && identity_rows) val = identity_rows == 1 ? v[n] : T(0);
       if (kSmooth) {
         val = xs + ss * (bs - val);
         dot += (double)bs * (double)val;
@@ -914,12 +907,22 @@ __device__ __forceinline__ void pc_electrons(const Geom& g, const WaveTile& w, i
 // an element with a nonzero c_q and then its c_q, else cflag = 0 and nothing
 // (depleted silicon, where n' underflows to exactly 0, and insulators).
 // norm2 accumulates F_i^2 over owned free nodes.
-template <typename TD, bool kQ = false>
+// The point is phi + lam delta as `trial` gives it: trial(phi_n, n).
+template <typename TD>
+struct TrialStep {
+  const TD* delta;   // NULL: phi itself
+  double lam;
+  __device__ __forceinline__ double operator()(double v, long n) const {
+    return delta ? v + lam * (double)delta[n] : v;
+  }
+};
+
+template <bool kQ = false, typename Trial>
 __device__ __forceinline__ void residual_tile(const Geom& g, const WaveTile& w, const Charge& ch,
                                               const double* __restrict__ eps, const uint8_t* __restrict__ semi,
                                               const Doping dop, const uint8_t* __restrict__ mask,
-                                              const double* __restrict__ phi, const TD* __restrict__ delta,
-                                              double lam, const double* __restrict__ fsheet,
+                                              const double* __restrict__ phi, const Trial& trial,
+                                              const double* __restrict__ fsheet,
                                               const double* __restrict__ fdiag, double* __restrict__ F,
                                               double* __restrict__ invdiag,
                                               double* __restrict__ diag_out, double* __restrict__ cq,
@@ -943,9 +946,7 @@ __device__ __forceinline__ void residual_tile(const Geom& g, const WaveTile& w, 
     const long o[4] = {0, 1, g.nx, g.nx + 1};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      double val = phi[b + o[k]];
-      if (delta) val += lam * (double)delta[b + o[k]];
-      f[k] = val;
+      f[k] = trial(phi[b + o[k]], b + o[k]);
     }
   };
   double fb[4], ft[4];
