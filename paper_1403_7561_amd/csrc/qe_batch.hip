@@ -1,27 +1,28 @@
 // Batched solve of many independent devices (a gate-voltage sweep over
-// uneven meshes): every instance marches in the same launches (qe_march.h).
+// uneven meshes).  Instances that fit are solved resident on the chip
+// (qe_resident.h), as many at a time as their boxes fit the compute units.
+// The others, and any whose launch could not get the chip to itself, march
+// together (qe_march.h): every launch advances all of them, so their number
+// bounds nothing but the traffic.
 //
-// The sweep's work is bound by memory traffic once the instances together
-// fill the chip, and by the number of launches below that; neither depends on
-// how large any one instance is.  (The persistent kernel this replaces gave
-// each instance one workgroup: the largest instance on one compute unit,
-// 475 ms for the 256 devices of 33x33x17 to 65x65x33 nodes, bounded the sweep.)
-//
-// The host checks the instances, lays out the workspace, picks the wave
-// tiles' chunk height (recorded in the tune cache), and queues ticks.
+// The host checks the instances, lays out the workspace, cuts the meshes,
+// picks the march's chunk height (recorded in the tune cache) and queues the
+// launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <map>
 #include <numeric>
 #include <sstream>
 #include <string>
 #include <vector>
 
-#include "qe_march.h"
+#include "qe_resident.h"
 
 namespace qe {
 
@@ -42,15 +43,17 @@ static size_t inst_bytes(const qe_problem& p) {
 
 // Per-instance results, read back in one copy.
 struct BatchHead {
-  size_t inst, blk_a, blk_b, state_a, state_b, counts, flags, done, total;
+  size_t inst, res, seats, blk_a, blk_b, state_a, state_b, counts, flags, done, total;
 };
 
 static BatchHead batch_head(int n, const qe_problem* probs) {
   BatchHead h;
-  size_t off = 0, na = 0, nb = 0;
+  size_t off = 0, na = 0, nb = 0, ns = 0;
   for (int i = 0; i < n; ++i) {
     na += make_wavemap(probs[i].nx, probs[i].ny, probs[i].nz, kMinKz).nblocks;
-    nb += march_blocks_b((long)probs[i].nx * probs[i].ny * probs[i].nz);
+    const long N = (long)probs[i].nx * probs[i].ny * probs[i].nz;
+    nb += march_blocks_b(N);
+    ns += std::min<long>(kResMaxWgs, N);
   }
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -58,6 +61,8 @@ static BatchHead batch_head(int n, const qe_problem* probs) {
     return o;
   };
   h.inst = take(sizeof(MarchInst) * n);
+  h.res = take(sizeof(ResInst) * n);
+  h.seats = take(sizeof(int2) * ns);
   h.blk_a = take(sizeof(int2) * na);
   h.blk_b = take(sizeof(int2) * nb);
   h.state_a = take(sizeof(MarchState) * n);
@@ -125,10 +130,117 @@ static void write_cache(const char* path, const std::string& key, int kz) {
   f << key << " " << kz << "\n";
 }
 
-// Zeroes the flags and the count of finished instances.
-__global__ __launch_bounds__(256) void k_batch_begin(int* flags, int n, unsigned int* done) {
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) flags[i] = 0;
+// Zeroes the flags, the states' phases and the count of finished instances.
+__global__ __launch_bounds__(256) void k_batch_begin(int* flags, MarchState* sb, int n, unsigned int* done) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    flags[i] = 0;
+    sb[i].phase = MARCH_RES;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;
+}
+
+// The cuts of all instances (nwg 0: does not fit), each mesh's found once.
+// When the batch fills the chip, the cuts with the least workgroup time;
+// otherwise each instance gets its share of the chip.
+static void batch_plans(int n, const qe_problem* probs, int wgs, std::vector<ResPlan>& plans) {
+  std::map<std::array<int, 3>, ResPlan> seen;
+  // (most: workgroups an instance may have; what its boxes exchange fits the
+  // room of the march's coefficients)
+  auto cut = [&](int most, bool share) {
+    seen.clear();
+    long total = 0;
+    for (int i = 0; i < n; ++i) {
+      const qe_problem& p = probs[i];
+      const std::array<int, 3> dims{p.nx, p.ny, p.nz};
+      auto it = seen.find(dims);
+      if (it == seen.end()) {
+        ResPlan q{};
+        const int fit = resident_fit((size_t)tile_slots(p.nx, p.ny, p.nz) * 64, (long)p.nx * p.ny * p.nz, wgs);
+        if (!resident_plan(p.nx, p.ny, p.nz, std::min(fit, most), share, q) &&
+            !resident_plan(p.nx, p.ny, p.nz, fit, share, q))
+          q.nwg = 0;
+        it = seen.emplace(dims, q).first;
+      }
+      plans[i] = it->second;
+      total += plans[i].nwg;
+    }
+    return total;
+  };
+  if (cut(wgs, true) < wgs) cut(std::max(1, wgs / n), false);
+}
+
+// The order of the instances: first fit decreasing into rows of wgs boxes, so
+// that the instances that are next to each other fill the chip.  us: time of
+// a CG iteration of all of them, each row as long as its slowest.
+static std::vector<int> batch_order(const std::vector<ResPlan>& plans, int wgs, double& us) {
+  std::vector<int> by(plans.size());
+  std::iota(by.begin(), by.end(), 0);
+  std::stable_sort(by.begin(), by.end(), [&](int l, int r) { return plans[l].nwg > plans[r].nwg; });
+  std::vector<std::vector<int>> rows;
+  std::vector<int> room;
+  size_t open = 0;   // rows before this one are full
+  for (int i : by) {
+    if (plans[i].nwg == 0) continue;
+    size_t r = open;
+    while (r < rows.size() && room[r] < plans[i].nwg) ++r;
+    if (r == rows.size()) {
+      rows.emplace_back();
+      room.push_back(wgs);
+    }
+    rows[r].push_back(i);
+    room[r] -= plans[i].nwg;
+    while (open < rows.size() && room[open] == 0) ++open;
+  }
+  std::vector<int> order;
+  us = 0.0;
+  for (const auto& row : rows) {
+    float slowest = 0.0f;
+    for (int i : row) slowest = std::max(slowest, plans[i].cost);
+    us += slowest;
+    order.insert(order.end(), row.begin(), row.end());
+  }
+  return order;
+}
+
+// Which instances are solved resident: those of up to a number of nodes, the
+// rest march; the number with the least time per CG iteration.  A tick of the
+// march costs its two launches and its traffic over all instances (measured
+// 12 us + 24 us per million nodes), so large instances are better marched
+// together than solved one or two at a time.  Measured, resident / march: 40
+// of 17x17x9 1.5 / 4.6 ms, 256 of 33x33x17 33 / 44, 64 of 49x49x25 66 / 49, 8
+// and 256 of 65x65x33 30 / 20 and 856 / 443.
+static std::vector<int> batch_split(const std::vector<long>& sizes, std::vector<ResPlan>& plans, int wgs) {
+  std::vector<long> most(sizes);
+  std::sort(most.begin(), most.end());
+  most.erase(std::unique(most.begin(), most.end()), most.end());
+  if (most.size() > 16) {   // (one in so many, and the largest)
+    std::vector<long> some;
+    for (size_t k = 1; k <= 16; ++k) some.push_back(most[k * most.size() / 16 - 1]);
+    most.swap(some);
+  }
+  auto split = [&](long m, std::vector<ResPlan>& q) {
+    double march = 0.0, us = 0.0;
+    q = plans;
+    for (size_t i = 0; i < q.size(); ++i) {
+      if (sizes[i] > m) q[i].nwg = 0;
+      if (q[i].nwg == 0) march += 24e-6 * sizes[i];
+    }
+    std::vector<int> order = batch_order(q, wgs, us);
+    return std::make_pair(us + (march > 0.0 ? 12.0 + march : 0.0), order);
+  };
+  std::vector<ResPlan> q, best(plans.size(), ResPlan{});
+  std::vector<int> order;
+  double least = split(-1, q).first;   // all marched
+  for (long m : most) {
+    const auto r = split(m, q);
+    if (r.first < least) {
+      least = r.first;
+      order = r.second;
+      best = q;
+    }
+  }
+  plans = best;
+  return order;
 }
 
 struct EventRing {
@@ -211,6 +323,18 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
   // workspace
   std::vector<char> head(H.state_a);
   MarchInst* hinst = reinterpret_cast<MarchInst*>(head.data() + H.inst);
+  ResInst* hres = reinterpret_cast<ResInst*>(head.data() + H.res);
+  int2* seats = reinterpret_cast<int2*>(head.data() + H.seats);
+  std::vector<ResPlan> plans(n_inst);
+  const int wgs = resident_on() ? resident_wgs() : 0;
+  int n_seats = 0, placed = 0;
+  if (wgs > 0) {
+    batch_plans(n_inst, probs, wgs, plans);
+    for (int i : batch_split(sizes, plans, wgs)) {
+      ++placed;
+      for (int b = 0; b < plans[i].nwg; ++b) seats[n_seats++] = make_int2(i, b);
+    }
+  }
   int2* blk_a = reinterpret_cast<int2*>(head.data() + H.blk_a);
   int2* blk_b = reinterpret_cast<int2*>(head.data() + H.blk_b);
   MarchArgs a;
@@ -256,6 +380,28 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
     I.nslots = S;
     I.na = I.wm.nblocks;
     I.n_dir = p.n_dir;
+    ResInst& R = hres[i];
+    R.nx = p.nx;
+    R.ny = p.ny;
+    R.nz = p.nz;
+    R.n_dir = p.n_dir;
+    R.x = p.x;
+    R.y = p.y;
+    R.z = p.z;
+    R.eps = p.eps_r;
+    R.semi = p.semi;
+    R.dop = I.dop;
+    R.dir_id = p.dir_id;
+    R.dir_val = p.dir_val;
+    R.phi = phi[i];
+    // two vectors' room each
+    R.w0 = reinterpret_cast<unsigned long long*>(I.x);
+    R.w1 = reinterpret_cast<unsigned long long*>(I.z);
+    R.d = reinterpret_cast<unsigned long long*>(I.y);
+    R.part = reinterpret_cast<unsigned long long*>(I.c);
+    R.plan = plans[i];
+    R.flags = nullptr;
+    R.out = I.sb;
     for (int b = 0; b < I.na; ++b) blk_a[a.na++] = make_int2(i, b);
     for (int b = 0; b < I.nb; ++b) blk_b[a.nb++] = make_int2(i, b);
   }
@@ -277,7 +423,8 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
   auto hip_ok = [](hipError_t e) { return e == hipSuccess; };
   if (!hip_ok(hipMemcpyAsync(ws, head.data(), head.size(), hipMemcpyHostToDevice, s)))
     return fail(QE_ERR_HIP, "descriptor upload failed");
-  hipLaunchKernelGGL(k_batch_begin, dim3((n_inst + 255) / 256), dim3(256), 0, s, a.flags, n_inst, a.done);
+  hipLaunchKernelGGL(k_batch_begin, dim3((n_inst + 255) / 256), dim3(256), 0, s, a.flags,
+                     reinterpret_cast<MarchState*>(ws + H.state_b), n_inst, a.done);
   launch_march_validate(s, a);
   // nothing is solved unless every instance is valid
   std::vector<int> flags(n_inst);
@@ -294,18 +441,48 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
   if (f & 1) return fail(QE_ERR_INVALID_ARG, "eps_r must be finite and > 0");
   if (f & 2) return fail(QE_ERR_NONFINITE, "net_doping not finite or donors / acceptors not finite and >= 0");
   if (f & 4) return fail(QE_ERR_INVALID_ARG, "dir_id outside [-1, n_dir)");
-  hm.prog->word = 0;
-  a.prog = hm.prog_dev;
-  launch_march_stage(s, a);
-  EventRing ring;
-  if ((st = march_run(s, a, hm, ring.e, 0)) != QE_OK) return st;
-  if (n_boxes > 0) launch_march_count(s, a, bs, reinterpret_cast<double*>(ws + H.counts));
   std::vector<char> res(H.flags - H.state_b);
-  if (!hip_ok(hipGetLastError()) ||
-      !hip_ok(hipMemcpyAsync(res.data(), ws + H.state_b, res.size(), hipMemcpyDeviceToHost, s)) ||
-      !hip_ok(hipStreamSynchronize(s)))
-    return fail(QE_ERR_HIP, "batch kernel failed");
   const MarchState* hs = reinterpret_cast<const MarchState*>(res.data());
+  auto read_back = [&]() {
+    return hip_ok(hipGetLastError()) &&
+           hip_ok(hipMemcpyAsync(res.data(), ws + H.state_b, res.size(), hipMemcpyDeviceToHost, s)) &&
+           hip_ok(hipStreamSynchronize(s));
+  };
+  if (placed > 0) {
+    ResArgs ra;
+    std::memset(&ra, 0, sizeof(ra));
+    ra.inst = reinterpret_cast<const ResInst*>(ws + H.res);
+    ra.n_inst = n_inst;
+    ra.seats = reinterpret_cast<const int2*>(ws + H.seats);
+    ra.n_seats = n_seats;
+    ra.ticket = a.done + 16;
+    ra.abort = reinterpret_cast<unsigned long long*>(a.done + 32);
+    ra.ch = ch;
+    ra.atol = a.atol;
+    ra.rtol_max = a.rtol_max;
+    ra.newton_maxit = a.newton_maxit;
+    ra.ls_max = a.ls_max;
+    ra.krylov_maxit = a.krylov_maxit;
+    ra.lenient = 1;
+    ra.init = MARCH_LINEAR;
+    ra.apply = ra.zero_free = 1;
+    if ((st = launch_resident(s, ra, plans.data(), n_inst, wgs)) != QE_OK) return st;
+  }
+  bool all = placed == n_inst;
+  if (n_boxes > 0 && all) launch_march_count(s, a, bs, reinterpret_cast<double*>(ws + H.counts));
+  if (all) {
+    if (!read_back()) return fail(QE_ERR_HIP, "batch kernel failed");
+    for (int i = 0; i < n_inst; ++i) all = all && hs[i].phase == MARCH_DONE;
+  }
+  if (!all) {
+    hm.prog->word = 0;
+    a.prog = hm.prog_dev;
+    launch_march_stage(s, a);
+    EventRing ring;
+    if ((st = march_run(s, a, hm, ring.e, 0)) != QE_OK) return st;
+    if (n_boxes > 0) launch_march_count(s, a, bs, reinterpret_cast<double*>(ws + H.counts));
+    if (!read_back()) return fail(QE_ERR_HIP, "batch kernel failed");
+  }
   const double* hc = reinterpret_cast<const double*>(res.data() + (H.counts - H.state_b));
   qe_status worst = QE_OK;
   for (int i = 0; i < n_inst; ++i) {

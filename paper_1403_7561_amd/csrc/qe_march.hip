@@ -400,7 +400,9 @@ __global__ __launch_bounds__(kVecThreads) void k_march_validate(MarchArgs A) {
 
 // The Dirichlet mask, phi's Dirichlet values, the tile-major permittivity,
 // the z spacings and the first state of an instance whose checks found
-// nothing; one with validation flags set is finished without being touched.
+// nothing; one with validation flags set is finished without being touched,
+// and of several, those that a resident solve has finished are left as they
+// are.
 template <bool kOne>
 __global__ __launch_bounds__(kVecThreads) void k_march_stage(MarchArgs A) {
   int lb = blockIdx.x, id = 0;
@@ -413,6 +415,13 @@ __global__ __launch_bounds__(kVecThreads) void k_march_stage(MarchArgs A) {
     I = A.inst[id];
     lb = __builtin_amdgcn_readfirstlane(e.y);
   }
+  if (!kOne && I.sb->phase == MARCH_DONE) {
+    if (lb == 0 && threadIdx.x == 0) {
+      *I.sa = *I.sb;
+      march_count_done(A);
+    }
+    return;
+  }
   const bool bad = A.flags && A.flags[id] != 0;
   if (lb == 0 && threadIdx.x == 0) {
     MarchState S = {};
@@ -423,8 +432,7 @@ __global__ __launch_bounds__(kVecThreads) void k_march_stage(MarchArgs A) {
     S.lam = 1.0;
     *I.sa = S;
     *I.sb = S;
-    if (bad && atomicAdd(A.done, 1u) == (unsigned int)A.n_inst - 1u && A.prog)
-      __hip_atomic_store(&A.prog->word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (bad) march_count_done(A);
   }
   if (bad) return;
   const long t0 = (long)lb * kVecThreads + threadIdx.x, stride = (long)I.nb * kVecThreads;

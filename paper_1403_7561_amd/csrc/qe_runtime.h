@@ -77,6 +77,8 @@ struct MgRun {
 
 // One call's view of a problem, its workspace and its stream.
 struct MarchArgs;
+struct ResArgs;
+struct ResPlan;
 struct Context {
   qe_problem prob;
   Geom g;
@@ -109,6 +111,7 @@ struct Context {
   qe_status init(const qe_problem* p, const Charge& ch, void* ws, size_t ws_bytes, void* stream, int kz = 0,
                  bool no_alloc = false, int wave_kz = 0);
   MarchArgs march_args(const Charge& ch, const qe_options* o, double* phi, double newton_rtol);
+  ResArgs resident_args(const MarchArgs& a, const ResPlan& plan, const int* flags);
   Doping doping() const;
   // Device-side checks of the problem's arrays (coordinates, Dirichlet ids
   // and values, eps_r, doping, sheets, states) and of phi: one round trip.

@@ -18,8 +18,7 @@
 
 #include "../../include/qe.h"
 #include "qe_kernels.h"
-#include "qe_march.h"
-#include "qe_runtime.h"
+#include "qe_resident.h"
 
 namespace qe {
 
@@ -190,6 +189,11 @@ static double env_double(const char* name, double dflt) {
   const char* v = getenv(name);
   return v ? atof(v) : dflt;
 }
+
+// QE_RESIDENT=0: the march also where a resident solve would fit (tests).
+bool resident_on() { return env_int("QE_RESIDENT", 1) != 0; }
+// QE_RESIDENT_POLLS: polls after which a wait of a resident solve gives up (tests).
+int resident_polls() { return (int)std::max(0l, std::min(2000000l, (long)env_int("QE_RESIDENT_POLLS", 0))); }
 
 static const int kCountBlocks = 256;
 
@@ -603,6 +607,49 @@ MarchArgs Context::march_args(const Charge& ch, const qe_options* o, double* phi
   a.flags = reinterpret_cast<int*>(ws + lay.flags);
   a.done = u32(lay.counters) + 8;
   return a;
+}
+
+// The same as a resident solve, in this call's workspace.
+ResArgs Context::resident_args(const MarchArgs& a, const ResPlan& plan, const int* flags) {
+  ResArgs R;
+  std::memset(&R, 0, sizeof(R));
+  ResInst& I = R.one;
+  I.nx = prob.nx;
+  I.ny = prob.ny;
+  I.nz = prob.nz;
+  I.n_dir = prob.n_dir;
+  I.x = prob.x;
+  I.y = prob.y;
+  I.z = prob.z;
+  I.eps = prob.eps_r;
+  I.semi = prob.semi;
+  I.dop = doping();
+  I.dir_id = prob.dir_id;
+  I.dir_val = prob.dir_val;
+  I.phi = a.one.phi;
+  // two vectors' room each: F and x, r and p, y and z follow each other
+  I.w0 = reinterpret_cast<unsigned long long*>(ws + lay.F);
+  I.w1 = reinterpret_cast<unsigned long long*>(ws + lay.r);
+  I.d = reinterpret_cast<unsigned long long*>(ws + lay.y);
+  I.plan = plan;
+  I.flags = flags;
+  I.out = a.one.sb;
+  // the Gauss-point coefficients' room: the march's, not the resident solve's
+  I.part = reinterpret_cast<unsigned long long*>(ws + lay.c);
+  R.n_inst = 1;
+  R.ticket = u32(lay.counters) + 9;
+  R.abort = reinterpret_cast<unsigned long long*>(ws + lay.flags) + 1;
+  R.ch = a.ch;
+  R.atol = a.atol;
+  R.rtol_max = a.rtol_max;
+  R.newton_rtol = a.newton_rtol;
+  R.newton_maxit = a.newton_maxit;
+  R.ls_max = a.ls_max;
+  R.krylov_maxit = a.krylov_maxit;
+  R.init = a.init;
+  R.apply = a.apply;
+  R.zero_free = a.zero_free;
+  return R;
 }
 
 // Jacobi-PCG on J x = sign*b (free rows).  Returns the CG status through
@@ -1306,12 +1353,25 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       return hipMemcpyAsync(&S, a.one.sb, sizeof(S), hipMemcpyDeviceToHost, cx.s) == hipSuccess &&
              hipStreamSynchronize(cx.s) == hipSuccess && hipGetLastError() == hipSuccess;
     };
-    a.flags = const_cast<int*>(flags);
-    if (hm.prog) hm.prog->word = 0;
-    a.prog = hm.prog_dev;
-    launch_march_stage(cx.s, a);
-    if ((st = march_run(cx.s, a, hm, cx.events, o->check_every)) != QE_OK) return finish(st, r, rep);
-    if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
+    S.phase = MARCH_RES;
+    ResPlan plan;
+    // (what the boxes exchange fits the coefficients' room)
+    const int wgs = resident_fit((size_t)cx.nslots * 64, cx.N, resident_wgs());
+    if (resident_on() && resident_plan(p->nx, p->ny, p->nz, wgs, false, plan)) {
+      ResArgs ra = cx.resident_args(a, plan, flags);
+      if ((st = launch_resident(cx.s, ra, &plan, 1, wgs)) != QE_OK) return finish(st, r, rep);
+      if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
+    }
+    if (S.phase != MARCH_DONE) {
+      // no cut fits, or the workgroups did not get the chip to themselves
+      // (phi is then as it was)
+      a.flags = const_cast<int*>(flags);
+      if (hm.prog) hm.prog->word = 0;
+      a.prog = hm.prog_dev;
+      launch_march_stage(cx.s, a);
+      if ((st = march_run(cx.s, a, hm, cx.events, o->check_every)) != QE_OK) return finish(st, r, rep);
+      if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
+    }
     if (S.flags) return finish(Context::flag_error(S.flags), r, rep);
     if (linear) r.init_krylov_iters = S.init_kry;
     r.krylov_iters += S.kry;

@@ -501,7 +501,7 @@ def qe_batch_workspace_bytes(probs, opts=None):
 
 def qe_solve_batch(probs, phys=None, opts=None, phis=None, boxes=(), tune_cache=None, ws=None,
                    check=True):
-    """Solve many devices in one persistent launch.  Returns (phis, counts
+    """Solve many devices in the same launches.  Returns (phis, counts
     [n_inst, n_boxes], reports)."""
     torch = _torch()
     lib = load_library()
