@@ -10,13 +10,14 @@
 // there and the J.v writes zero rows.
 //
 // One LOBPCG iteration: residuals R = H'X - M X diag(lambda) and their norms
-// (device), soft locking of converged columns (host decision), W = D^-1 R
-// for the active ones and its H', M products, the Gram matrices of
+// (device), soft locking of converged columns (host decision), W = an
+// approximate (H' - shift M)^-1 R by a few Chebyshev steps on the Jacobi
+// scaling (each one sweep over the active columns) for the active ones and its
+// H', M products, the Gram matrices of
 // [X, W, P] under H' and M (one pass over the three blocks on the FP64
-// matrix cores), the small
-// generalized eigenproblem on the host (column scaling, Cholesky, cyclic
-// Jacobi), and the new X, P (with their products) in one streaming pass
-// (the update is memory bound: k reads and 2 nb writes per row).
+// matrix cores), the small generalized eigenproblem on the host
+// (rayleigh_ritz), and the new X, P (with their products) in one streaming
+// pass (the update is memory bound: k reads and 2 nb writes per row).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,7 +36,24 @@ namespace qe {
 static const double kHB2M = 1.054571817e-34 * 1.054571817e-34 / (2.0 * 9.1093837015e-31) / 1.602176634e-19 * 1e18;
 constexpr int kSchBlocks = 256;
 constexpr int kMaxCols = QE_MAX_EIG + 2;
+static_assert(kMaxCols <= 18, "k_sch_dots' instances");
 constexpr int kGramBlocks = 512;   // row ranges of the Gram matrices
+constexpr int kDotBlocks = 64;     // row ranges of W's products with X
+constexpr double kSchGap = 0.1;    // eV from sigma up to the lowest V
+
+// The preconditioner of the residuals: kChebSteps Chebyshev steps for the
+// eigenvalues of D^-1 (H' - shift M) from 1 / kChebRatio of their bound up to
+// the bound, with the shift at the lowest V (so that the operator stays SPD)
+// until the lowest state's residual is below kChebShiftTol, then that part of
+// the way from there to its energy.  A step costs a sweep like the operators'
+// own; an iteration of LOBPCG costs five to ten of them (Gram matrices, update,
+// norms, the small eigenproblem on the host).  Iterations and time of 8 states
+// at 129x129x65 / 10 at 97x80x100 / 16 at 65x65x33, by the steps (ratio): 1
+// (Jacobi alone) 131, 25.6 ms / 119 / 130; 4 (16) 38, 13.0 ms / 38, 13.2 / 52,
+// 21.2; 5 (20) 37, 12.6 / 38, 12.8 / 45, 19.1; 6 (20) 33, 12.5 / 38, 13.9 / 49,
+// 21.2; 5 (20) with the first shift throughout 44, 15.3 / 47, 16.8 / 61, 26.6.
+constexpr int kChebSteps = 5;
+constexpr double kChebRatio = 20.0, kChebShift = 0.85, kChebShiftTol = 1e-3;
 
 // Input checks: bit 1 inv_mass not finite / positive, 2 v0 not finite, 4 phi not finite.
 __global__ __launch_bounds__(kVecThreads) void k_sch_validate(long E, long N, const double* __restrict__ inv_mass,
@@ -96,11 +114,19 @@ __global__ __launch_bounds__(kVecThreads) void k_sch_vmin(Geom g, const double* 
 
 // Tile-major operator data: kinetic weights (hbar^2/2m0)(m0/m*_a) along
 // a = x, y, z (three planes of nslots) and the Gauss-point coefficients
-// W (V_q - sigma) of H', W of M.
+// W (V_q - sigma) of H', W of M.  Also an upper bound of the eigenvalues of
+// D^-1 H' (k_sch_diag's D) into bound (its bits; nonnegative doubles order like
+// integers; zeroed before): the largest ratio, over the elements, of the
+// largest eigenvalue of H's element matrix -- at most half the largest kinetic
+// weight (the wave along one axis) plus the largest potential coefficient --
+// to the smallest of the element's contributions to D.
 __global__ __launch_bounds__(kVecThreads) void k_sch_coef(Geom g, const double* __restrict__ inv_mass,
                                                          const double* __restrict__ v0,
                                                          const double* __restrict__ phi, double sigma, double hb2m,
-                                                         double* __restrict__ eH, double* __restrict__ cH) {
+                                                         double* __restrict__ eH, double* __restrict__ cH,
+                                                         unsigned long long* __restrict__ bound) {
+  __shared__ double sred[kVecThreads / 64];
+  double most = 0.0;
   const long E = (long)(g.nx - 1) * (g.ny - 1) * (g.nz - 1);
   const int tgx = (g.nx + 6) / 7, tgy = (g.ny + 6) / 7;
   for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += (long)gridDim.x * blockDim.x) {
@@ -110,6 +136,9 @@ __global__ __launch_bounds__(kVecThreads) void k_sch_coef(Geom g, const double* 
     const long sy = g.nx, sz = (long)g.nx * g.ny;
     double q[8] = {phi[n0], phi[n0 + 1], phi[n0 + sy], phi[n0 + sy + 1],
                    phi[n0 + sz], phi[n0 + sz + 1], phi[n0 + sz + sy], phi[n0 + sz + sy + 1]};
+    double high = q[0];
+#pragma unroll
+    for (int t = 1; t < 8; ++t) high = fmax(high, q[t]);
     gauss_interp(q);
     const double W = (g.x[i + 1] - g.x[i]) * (g.y[j + 1] - g.y[j]) * (g.z[k + 1] - g.z[k]) * 0.125;
     const double ve = v0[e];
@@ -121,6 +150,21 @@ __global__ __launch_bounds__(kVecThreads) void k_sch_coef(Geom g, const double* 
 #pragma unroll
     for (int a = 0; a < 3; ++a) eH[a * nslots + sl] = hb2m * inv_mass[a * E + e];
     store8(cH + 8 * sl, ch);
+    const double hx = g.x[i + 1] - g.x[i], hy = g.y[j + 1] - g.y[j], hz = g.z[k + 1] - g.z[k];
+    const double sx = hb2m * inv_mass[e] * (hy * hz / hx), sy_ = hb2m * inv_mass[E + e] * (hx * hz / hy),
+                 sz_ = hb2m * inv_mass[2 * E + e] * (hx * hy / hz);
+    double top = ch[0];
+#pragma unroll
+    for (int t = 1; t < 8; ++t) top = fmax(top, ch[t]);
+    const double low = (sx + sy_ + sz_) * (1.0 / 9.0) + W * (8.0 / 27.0) * fmax(ve - high - sigma, 0.0);
+    most = fmax(most, (0.5 * fmax(sx, fmax(sy_, sz_)) + top) / low);
+  }
+  for (int o = 32; o > 0; o >>= 1) most = fmax(most, __shfl_down(most, o, 64));
+  if ((threadIdx.x & 63) == 0) sred[threadIdx.x >> 6] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kVecThreads / 64; ++w) most = fmax(most, sred[w]);
+    atomicMax(bound, (unsigned long long)__double_as_longlong(most));
   }
 }
 
@@ -156,9 +200,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
   const bool ok[2] = {true, ca + 1 < c0 + ncols};
   const int cb = ok[1] ? ca + 1 : ca;
   const double* const zc[2] = {Z + (long)ca * N, Z + (long)cb * N};
-  double* const yh[2] = {HZ + (long)ca * N, HZ + (long)cb * N};
-  double* const ym[2] = {MZ + (long)ca * N, MZ + (long)cb * N};
-  jv_tile_hm(g, t, wm.kz, eH, cH, mb, zc, yh, ym, ok);
+  HmProducts out;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    out.yh[c] = HZ + (long)(c ? cb : ca) * N;
+    out.ym[c] = MZ + (long)(c ? cb : ca) * N;
+  }
+  jv_tile_hm(g, t, wm.kz, eH, cH, mb, zc, ok, out);
+}
+
+// A Chebyshev step (HmChebyshev) on ncols columns of stride N, two per block
+// like k_sch_apply: d -> dn, r and z updated.  Bound like k_sch_apply by the
+// latency of a wave's layers at two waves per SIMD; the node's own values are
+// loaded ahead of a layer's arithmetic.
+template <bool kFirst, bool kLast>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_sch_cheb(
+    Geom g, WaveMap wm, const double* __restrict__ eH, const double* __restrict__ cH,
+    const unsigned int* __restrict__ mbits, long N, int ncols, const double* __restrict__ dinv, double shift,
+    double c1, double c2, const double* __restrict__ d, double* __restrict__ dn, double* __restrict__ r,
+    double* __restrict__ z) {
+  const int w = __builtin_amdgcn_readfirstlane(wave_of_block(blockIdx.x, wm) * 4 + (threadIdx.x >> 6));
+  const bool active = w < wm.nwaves;
+  int wx, wy, wz;
+  wave_tile_of(w, wm, wx, wy, wz);
+  const WaveTile t(g, wx, wy, wz, wm.kz, threadIdx.x & 63, active);
+  const unsigned int mb = mbits[64L * min(w, wm.nwaves - 1) + (threadIdx.x & 63)];
+  const int ca = 2 * (int)blockIdx.y;
+  const bool ok[2] = {true, ca + 1 < ncols};
+  HmChebyshev<kFirst, kLast> out;
+  out.dinv = dinv;
+  out.shift = shift;
+  out.c1 = c1;
+  out.c2 = c2;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const long o = (long)(ok[c] ? ca + c : ca) * N;
+    out.d[c] = d + o;
+    out.dn[c] = dn + o;
+    out.r[c] = r + o;
+    out.z[c] = z + o;
+  }
+  jv_tile_hm(g, t, wm.kz, eH, cH, mb, out.d, ok, out);
 }
 
 // Jacobi preconditioner: 1 / (kinetic diagonal + consistent-mass diagonal
@@ -336,15 +418,83 @@ __global__ __launch_bounds__(kVecThreads) void k_sch_rowsum(const double* __rest
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// W[dst] = D^-1 (H'x - lam M x) for the mapped columns.
+// The first Chebyshev step from z = 0: r = H'x - lam M x of the mapped columns
+// and d = scale D^-1 r, into consecutive columns.
 __global__ __launch_bounds__(kVecThreads) void k_sch_precond(long N, ColMap cm, const double* __restrict__ HX,
                                                             const double* __restrict__ MX,
-                                                            const double* __restrict__ dinv, double* __restrict__ Z) {
+                                                            const double* __restrict__ dinv, double scale,
+                                                            double* __restrict__ r, double* __restrict__ d) {
   const int c = blockIdx.y;
-  const long o = (long)cm.src[c] * N, d = (long)cm.dst[c] * N;
+  const long o = (long)cm.src[c] * N, t = (long)c * N;
   const double lam = cm.lam[c];
-  for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x)
-    Z[d + n] = dinv[n] * (HX[o + n] - lam * MX[o + n]);
+  for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x) {
+    const double v = HX[o + n] - lam * MX[o + n];
+    r[t + n] = v;
+    d[t + n] = scale * (dinv[n] * v);
+  }
+}
+
+// Per block, for two columns of W: partial sums of their products with MX's
+// nb <= NB columns, part[(column * kMaxCols + i) * gridDim.x + block].  Columns
+// past nb repeat the last (unused): without branches a row's loads are all in
+// flight together.
+template <int NB>
+__global__ __launch_bounds__(kVecThreads) void k_sch_dots(long N, int nb, int na, const double* __restrict__ MX,
+                                                         const double* __restrict__ W, double* __restrict__ part) {
+  constexpr int kW = kVecThreads / 64;
+  __shared__ double sred[2 * kMaxCols][kW];
+  const int c0 = 2 * (int)blockIdx.y, c1 = min(c0 + 1, na - 1);
+  double acc[2][NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) acc[0][i] = acc[1][i] = 0.0;
+  for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x) {
+    const double w0 = W[(long)c0 * N + n], w1 = W[(long)c1 * N + n];
+    double m[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) m[i] = MX[(long)min(i, nb - 1) * N + n];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      acc[0][i] += m[i] * w0;
+      acc[1][i] += m[i] * w1;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      double v = acc[c][i];
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+      if ((threadIdx.x & 63) == 0) sred[c * kMaxCols + i][threadIdx.x >> 6] = v;
+    }
+  __syncthreads();
+  const int c = threadIdx.x / kMaxCols, i = threadIdx.x % kMaxCols;
+  if (c < 2 && i < nb && c0 + c < na) {
+    double v = 0.0;
+    for (int w = 0; w < kW; ++w) v += sred[c * kMaxCols + i][w];
+    part[((long)(c0 + c) * kMaxCols + i) * gridDim.x + blockIdx.x] = v;
+  }
+}
+
+// W's column blockIdx.y without its components along X (M-orthonormal): W -=
+// X (MX)^T W, the products from k_sch_dots' partials (kDotBlocks of each,
+// summed in a fixed order).
+__global__ __launch_bounds__(kVecThreads) void k_sch_project(long N, int nb, const double* __restrict__ part,
+                                                            const double* __restrict__ X, double* __restrict__ W) {
+  static_assert(kDotBlocks == 64, "one lane per partial");
+  __shared__ double g[kMaxCols];
+  const int c = blockIdx.y;
+  for (int i = threadIdx.x >> 6; i < nb; i += kVecThreads / 64) {
+    double v = part[((long)c * kMaxCols + i) * kDotBlocks + (threadIdx.x & 63)];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if ((threadIdx.x & 63) == 0) g[i] = v;
+  }
+  __syncthreads();
+  for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long)gridDim.x * blockDim.x) {
+    double w = W[(long)c * N + n];
+#pragma unroll 6
+    for (int i = 0; i < nb; ++i) w -= g[i] * X[(long)i * N + n];
+    W[(long)c * N + n] = w;
+  }
 }
 
 // The Rayleigh-Ritz update of one operator's block (blockIdx.y: the block
@@ -799,8 +949,12 @@ static qe_status sch_core(const qe_problem* p, const double* inv_mass, const dou
   g.rdz = f64(L.rdz);
   g.hz = g.rdz + (p->nz - 1);
   launch_stage_rdz(s, p->nz, p->z, f64(L.rdz));
+  unsigned long long* dbound = reinterpret_cast<unsigned long long*>(ws + L.flags);
+  double bound = 0.0;
+  QE_TRY(ck(hipMemsetAsync(dbound, 0, sizeof(*dbound), s), "memset"));
   hipLaunchKernelGGL(k_sch_coef, dim3(vb), dim3(kVecThreads), 0, s, g, inv_mass, v0, phi, sigma, kHB2M,
-                     f64(L.eH), f64(L.cH));
+                     f64(L.eH), f64(L.cH), dbound);
+  QE_TRY(ck(hipMemcpyAsync(&bound, dbound, sizeof(bound), hipMemcpyDeviceToHost, s), "copy"));
   uint8_t* mask = reinterpret_cast<uint8_t*>(ws + L.mask);
   if (fixed)
     QE_TRY(ck(hipMemcpyAsync(mask, fixed, N, hipMemcpyDeviceToDevice, s), "copy"));
@@ -816,6 +970,48 @@ static qe_status sch_core(const qe_problem* p, const double* inv_mass, const dou
   auto apply = [&](int c0, int n) {
     hipLaunchKernelGGL(k_sch_apply, dim3(wm.nblocks, (n + 1) / 2), dim3(256), 0, s, g, wm, f64(L.eH), f64(L.cH),
                        mbits, N, c0, n, Z, HZ, MZ);
+  };
+  // W = Z's columns nb .. from the mapped columns' residuals.  The scratch
+  // columns are those of HZ and MZ at W's place (apply writes them afterwards)
+  // and the third block of columns, which hold nothing (P is read where it is).
+  auto precondition = [&](const ColMap& cm, double above) {
+    double* const W = Z + (long)nb * N;
+    const double theta = 0.5 * bound * (1.0 + 1.0 / kChebRatio), delta = 0.5 * bound * (1.0 - 1.0 / kChebRatio);
+    const double s1 = theta / delta, shift = std::max(0.0, kSchGap + above);
+    double rho = 1.0 / s1;
+    double *r = HZ + 2L * nb * N, *d = MZ + (long)nb * N, *dn = MZ + 2L * nb * N;
+    hipLaunchKernelGGL(k_sch_precond, dim3(kSchBlocks, cm.n), dim3(kVecThreads), 0, s, N, cm, HZ, MZ, f64(L.dinv),
+                       1.0 / theta, r, d);
+    for (int k = 1; k < kChebSteps; ++k) {
+      const double next = 1.0 / (2.0 * s1 - rho), c1 = next * rho, c2 = 2.0 * next / delta;
+      auto step = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(wm.nblocks, (cm.n + 1) / 2), dim3(256), 0, s, g, wm, f64(L.eH), f64(L.cH),
+                           mbits, N, cm.n, f64(L.dinv), shift, c1, c2, d, dn, r, W);
+      };
+      if (k == 1)
+        step(k_sch_cheb<true, false>);
+      else if (k + 1 < kChebSteps)
+        step(k_sch_cheb<false, false>);
+      else
+        step(k_sch_cheb<false, true>);
+      rho = next;
+      std::swap(d, dn);
+    }
+    // The preconditioner weights a residual's components along X, which are
+    // rounding errors, by up to 10^3 more than the rest: near convergence
+    // they are what W would consist of (seen: the smallest eigenvalue of the
+    // scaled Gram matrix down to 1e-14, then no convergence; 3e-7 without them).
+    auto dots = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(kDotBlocks, (cm.n + 1) / 2), dim3(kVecThreads), 0, s, N, nb, cm.n, MZ, W,
+                         f64(L.gpart));
+    };
+    if (nb <= 6)
+      dots(k_sch_dots<6>);
+    else if (nb <= 12)
+      dots(k_sch_dots<12>);
+    else
+      dots(k_sch_dots<18>);
+    hipLaunchKernelGGL(k_sch_project, dim3(kSchBlocks, cm.n), dim3(kVecThreads), 0, s, N, nb, f64(L.gpart), Z, W);
   };
   std::vector<double> hG(2 * (size_t)K * K), lam, Cm;
   // Gram matrices of the first k columns, Rayleigh-Ritz, and the new X (and
@@ -870,9 +1066,11 @@ static qe_status sch_core(const qe_problem* p, const double* inv_mass, const dou
     QE_TRY(ck(hipStreamSynchronize(s), "sync"));
     active.clear();
     bool done = true;
+    double rel0 = 0.0;   // of the lowest state
     for (int c = 0; c < nb; ++c) {
       const double r = std::sqrt(sums[3 * c]), h = std::sqrt(sums[3 * c + 1]), m = std::sqrt(sums[3 * c + 2]);
       const double rel = r / std::max(h + std::fabs(lam[c]) * m, 1e-300);
+      if (c == 0) rel0 = rel;
       if (!std::isfinite(rel)) return fail(QE_ERR_NONFINITE, "non-finite residual in the eigensolver");
       if (rel > tol) {
         active.push_back(c);
@@ -884,17 +1082,16 @@ static qe_status sch_core(const qe_problem* p, const double* inv_mass, const dou
       break;
     }
     if (it == maxit) break;
-    // W = D^-1 R for the active columns, after X in Z; P's active columns after W
+    // W for the active columns, after X in Z
     const int na = (int)active.size();
     ColMap wmap;
     std::memset(&wmap, 0, sizeof(wmap));
     wmap.n = na;
     for (int a = 0; a < na; ++a) {
       wmap.src[a] = active[a];
-      wmap.dst[a] = nb + a;
       wmap.lam[a] = lam[active[a]];
     }
-    hipLaunchKernelGGL(k_sch_precond, dim3(kSchBlocks, na), dim3(kVecThreads), 0, s, N, wmap, HZ, MZ, f64(L.dinv), Z);
+    precondition(wmap, rel0 < kChebShiftTol ? kChebShift * (lam[0] - kSchGap) : 0.0);
     apply(nb, na);
     const int k = nb + na;
     PCols pc;
@@ -980,7 +1177,7 @@ qe_status qe_schrodinger_solve(const qe_problem* p, const qe_schrodinger* sp, co
   if (hf[0] & 4) return fail(QE_ERR_NONFINITE, "phi not finite");
   double vmin = INFINITY;
   for (double v : hp) vmin = std::min(vmin, v);
-  const double sigma = vmin - 0.1;   // eV below every V: H - sigma M is SPD
+  const double sigma = vmin - kSchGap;   // H - sigma M is SPD
   const BoxMap whole{nx, ny, nz, 0, 0, 0, nx, ny};
   // Every node outside the free nodes' bounding box grown by one node is
   // fixed and touches only elements whose nodes are all fixed, so psi is 0

@@ -597,28 +597,92 @@ __device__ __forceinline__ bool jv_tile_cg(const Geom& g, const WaveTile& w, int
 // basis in that subspace); outputs are 0 on owned nodes whose bit in mbits
 // (bit L - Lbeg: the node of layer L is fixed) is set.  col_ok[1] = false:
 // the second column is absent (its resources are empty: zeros in, no stores).
+//
+// out takes the products of every owned node: begin() gets the first value
+// and the size of the tile's part of a column, fetch() runs ahead of a layer's
+// arithmetic (loads that put() needs), put() takes (H v, M v) of one node.
 struct HmStage {
   double f[2][4];
   double e[3];   // kinetic weights along x, y, z
   double c[8];
 };
 
+// The products themselves.
+struct HmProducts {
+  using IO = BufIO<double>;
+  double *yh[2], *ym[2];
+  __amdgpu_buffer_rsrc_t rh[2], rm[2];
+  __device__ __forceinline__ void begin(long first, long bytes, const bool col_ok[2]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      rh[c] = buf_res(yh[c] + first, col_ok[c] ? bytes : 0);
+      rm[c] = buf_res(ym[c] + first, col_ok[c] ? bytes : 0);
+    }
+  }
+  __device__ __forceinline__ void fetch(unsigned int, unsigned int) {}
+  __device__ __forceinline__ void put(int c, double h, double m, unsigned int v, unsigned int so) {
+    IO::st(rh[c], h, v, so);
+    IO::st(rm[c], m, v, so);
+  }
+};
+
+// A step of the Chebyshev iteration on (H - shift M) z = r with Jacobi
+// scaling: r -= (H - shift M) d, d' = c1 d + c2 D^-1 r, z += d', where the
+// sweep's input is d.  kFirst: z = d + d' (z holds nothing yet); kLast: r and
+// d' are not needed any more.
+template <bool kFirst, bool kLast>
+struct HmChebyshev {
+  using IO = BufIO<double>;
+  const double* d[2];
+  double *dn[2], *r[2], *z[2];
+  const double* dinv;
+  double shift, c1, c2;
+  __amdgpu_buffer_rsrc_t rd[2], rn[2], rr[2], rz[2], ri;
+  double vd[2], vr[2], vz[2], vi;
+  __device__ __forceinline__ void begin(long first, long bytes, const bool col_ok[2]) {
+    ri = buf_res(dinv + first, bytes);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const long n = col_ok[c] ? bytes : 0;
+      rd[c] = buf_res(d[c] + first, n);
+      rn[c] = buf_res(dn[c] + first, n);
+      rr[c] = buf_res(r[c] + first, n);
+      rz[c] = buf_res(z[c] + first, n);
+    }
+  }
+  __device__ __forceinline__ void fetch(unsigned int v, unsigned int so) {
+    vi = IO::ld(ri, v, so);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      vd[c] = IO::ld(rd[c], v, so);
+      vr[c] = IO::ld(rr[c], v, so);
+      if constexpr (!kFirst) vz[c] = IO::ld(rz[c], v, so);
+    }
+  }
+  __device__ __forceinline__ void put(int c, double h, double m, unsigned int v, unsigned int so) {
+    const double res = vr[c] - (h - shift * m);
+    const double dv = c1 * vd[c] + c2 * (vi * res);
+    if constexpr (!kLast) {
+      IO::st(rr[c], res, v, so);
+      IO::st(rn[c], dv, v, so);
+    }
+    IO::st(rz[c], (kFirst ? vd[c] : vz[c]) + dv, v, so);
+  }
+};
+
+template <typename Out>
 __device__ __forceinline__ void jv_tile_hm(const Geom& g, const WaveTile& w, int kz, const double* __restrict__ eH,
                                            const double* __restrict__ cH, unsigned int mbits,
-                                           const double* const zc[2], double* const yh[2], double* const ym[2],
-                                           const bool col_ok[2]) {
+                                           const double* const zc[2], const bool col_ok[2], Out& out) {
   using IO = BufIO<double>;
   constexpr unsigned int B = 8;
   const long sxy = w.sxy, sl = w.slot_layer;
   const int Pb = min(max(w.Lbeg, 0), g.nz - 2);
   const long vbytes = (long)(g.nz - Pb) * sxy * B;
-  __amdgpu_buffer_rsrc_t rz[2], rh[2], rm[2];
+  __amdgpu_buffer_rsrc_t rz[2];
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    rz[c] = buf_res(zc[c] + sxy * Pb, col_ok[c] ? vbytes : 0);
-    rh[c] = buf_res(yh[c] + sxy * Pb, col_ok[c] ? vbytes : 0);
-    rm[c] = buf_res(ym[c] + sxy * Pb, col_ok[c] ? vbytes : 0);
-  }
+  for (int c = 0; c < 2; ++c) rz[c] = buf_res(zc[c] + sxy * Pb, col_ok[c] ? vbytes : 0);
+  out.begin(sxy * Pb, vbytes, col_ok);
   // eH holds three planes of tile-major weights (x, y, z), nslots apart
   const long nslots = sl * (g.nz - 1);
   __amdgpu_buffer_rsrc_t re[3];
@@ -683,6 +747,9 @@ __device__ __forceinline__ void jv_tile_hm(const Geom& g, const WaveTile& w, int
   auto step = [&](int L, HmStage& cur, HmStage& nxt, auto next_tag) {
     constexpr bool kNext = decltype(next_tag)::value;
     const int j = L - w.Lbeg;
+    const bool st = L >= w.k0 && L <= w.Lend;
+    const unsigned int os = st ? o_n : kBufOob;
+    out.fetch(os, s_node(L));
     if constexpr (kNext) {
       IO::ld8(rc, o_cl(L + 1), 8 * s_elem(L + 1), nxt.c);
 #pragma unroll
@@ -704,9 +771,7 @@ __device__ __forceinline__ void jv_tile_hm(const Geom& g, const WaveTile& w, int
     const double m0 = V * (1.0 / 64.0), m1 = V * (1.0 / 192.0), m2 = V * (1.0 / 576.0), m3 = V * (1.0 / 1728.0);
     const double db[8] = {0.125, 0.07216878364870322, 0.07216878364870322, 0.041666666666666664,
                           0.07216878364870322, 0.041666666666666664, 0.041666666666666664, 0.024056261216234407};
-    const bool st = L >= w.k0 && L <= w.Lend;
     const bool fixed = (mbits >> j) & 1u;
-    const unsigned int os = st ? o_n : kBufOob;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       double Tt[4], vt[8], oh[8], om[8], q[8];
@@ -751,8 +816,7 @@ __device__ __forceinline__ void jv_tile_hm(const Geom& g, const WaveTile& w, int
       double vh = (crH[3] + lane_next(crH[2])) + shfl_down_t(crH[1] + lane_next(crH[0]), 8);
       double vm = (crM[3] + lane_next(crM[2])) + shfl_down_t(crM[1] + lane_next(crM[0]), 8);
       if (fixed) vh = vm = 0.0;
-      IO::st(rh[c], vh, os, s_node(L));
-      IO::st(rm[c], vm, os, s_node(L));
+      out.put(c, vh, vm, os, s_node(L));
 #pragma unroll
       for (int k = 0; k < 4; ++k) Tb[c][k] = Tt[k];
     }
