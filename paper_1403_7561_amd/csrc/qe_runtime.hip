@@ -1024,12 +1024,25 @@ static size_t seq_extra_bytes(const qe_problem* p, int levels) {
 static const long kMgMinNodes = 250000;
 static const long kMgMinCoarse = 2000;
 static const int kMgMaxLevels = 6;
-// AUTO: multigrid for CG tolerances at or below this one.  At the
-// 129x129x65 stack a V-cycle costs ~7 Jacobi iterations (its small levels
-// are launch- and latency-bound) and saves ~10x the iterations on the last
-// Newton steps; measured there, 1e-2 / 3e-2 / 1e-1 / every step gave
-// 13.4 / 13.4 / 13.5 / 15.0 ms per solve against 17.8 ms with Jacobi only.
-static const double kMgEta = 3e-2;
+// AUTO: multigrid for CG tolerances at or below kMgEta on meshes of up to
+// kMgLargeNodes nodes and with eigenstates (whose coarse levels evaluate the
+// states too); on larger ones at or below kMgEtaLarge, and above it when a
+// trial of kMgTrial iterations with Jacobi alone does not suffice, then for
+// the rest of the solve.  A V-cycle costs 4 to 7 Jacobi iterations and a solve
+// with it at the forcing term's cap of 0.3 takes 4 or 5; Jacobi takes 5 to 100
+// there, by the charge's share of the diagonal, which the mesh does not tell.
+// Measured with 3e-2 / 1e-1 / 3e-1 for all / 1e-1 and the trial, in ms: stack
+// at 113x97x49 10.4 / 10.2 / 10.6 / 9.8, at 129x129x65 15.3 / 13.5 / 11.8 /
+// 12.4, with Robin gates 23.6 / 21.8 / 19.3 / 19.5; at 200x160x81 37.1 / 33.3 /
+// 27.0 / 26.6; full charge at 145x129x73 17.1 / 15.2 / 20.2 / 16.2; junctions
+// of 366,000 and 1,010,000 nodes 20.9 / 19.0 / 14.0 / 13.5 and 50.5 / 42.4 /
+// 24.8 / 25.3; FP64 at 257x200x81 71.5 / 63.9 / 32.1 / 34.6; mixed at 257x257x129
+// 93.1 / 53.7 / 39.2 / 41.3.  A trial of 20 or 30 iterations: 12.7 / 13.0 at
+// 129x129x65, 15.2 / 15.2 for the full charge.  Below the line: 91x89x35 8.4 /
+// 8.3 / 9.2 / 8.9; with 16 states at 97x97x49 12.1 / 12.1 / 13.1 / 13.4.
+static const double kMgEta = 3e-2, kMgEtaLarge = 1e-1;
+static const long kMgLargeNodes = 350000;
+static const int kMgTrial = 12;
 // Smoothing steps on the coarsest mesh (at 129x129x65 with the weight below,
 // 2 / 4 / 6 gave 37 / 30 / 28 adjoint iterations in 7.6 / 6.9 / 6.9 ms and
 // solves of 12.0 / 11.0 / 11.3 ms; a fifth level, down to 9x9x5, measured
@@ -1062,13 +1075,6 @@ static const double kMgOmega = 1.8;
 // save (257x257x129: solve 88 -> 76 ms, adjoint 39 -> 34 ms; at 129x129x65
 // the multiplicative form is faster, 11.3 against 11.9 ms).
 static const long kMgAddTopNodes = 4000000;
-// On those meshes a V-cycle costs about two Jacobi iterations, so the AUTO
-// rule takes it from this CG tolerance on (257x257x129: 3e-2 / 5e-2 / 1e-1
-// / 2e-1 gave FP64 solves of 71.5 / 48.0 / 46.8 / 46.8 ms, mixed 50.4 /
-// 37.3 / 37.3 / 37.3; the same on its 129x129x65 coarse start as well
-// measured slower, 47.7, and at 129x129x65 itself 1e-1 made the solve 3 %
-// slower).
-static const double kMgEtaLarge = 1e-1;
 static double mg_omega() {
   const double w = env_double("QE_MG_OMEGA", kMgOmega);
   return (w > 0.0 && w < 2.0) ? w : kMgOmega;
@@ -1152,14 +1158,6 @@ static size_t extra_bytes(const qe_problem* p, int seq_levels) {
   return std::max(seq_extra_bytes(p, seq_levels), mg_extra_bytes(p));
 }
 
-// The AUTO threshold for a mesh of this many nodes (QE_MG_ETA overrides it
-// for every mesh).
-static double mg_eta(long nodes) {
-  const char* v = getenv("QE_MG_ETA");
-  if (v) return atof(v);
-  return nodes >= env_long("QE_MG_ADD_NODES", kMgAddTopNodes) ? kMgEtaLarge : kMgEta;
-}
-
 // One call's multigrid levels: planned when the call may use them, set up
 // on first use, linearised at each potential a CG solve with them starts
 // from.
@@ -1167,11 +1165,23 @@ struct MgState {
   MgPlan plan;
   char* base = nullptr;
   bool possible = false, ready = false;
+  bool slow = false;   // a trial with Jacobi alone ran out
   Context cx[kMgMaxLevels];   // levels 1 .. nlev - 1
   MgGrid lv[kMgMaxLevels];
   MgRun run{};
 
   bool fp32 = false;   // the CG it serves runs in FP32 (mixed precision)
+
+  bool large() const {
+    const qe_problem& p = plan.pc[0];
+    return !p.quantum && (long)p.nx * p.ny * p.nz >= env_long("QE_MG_LARGE_NODES", kMgLargeNodes);
+  }
+  // Iterations that a Newton step's CG is tried with Jacobi alone before
+  // multigrid takes it (0: no trial).
+  int trial(const qe_options* o) const {
+    const int most = env_int("QE_MG_TRIAL", kMgTrial);
+    return possible && large() && !slow && o->precond == QE_PC_AUTO && most < o->krylov_maxit ? most : 0;
+  }
 
   // Whether multigrid can serve this call (an allocating entry point, a
   // large enough plain mesh, room in the workspace).
@@ -1185,7 +1195,9 @@ struct MgState {
     possible = mg_plan(p, base, plan) && ws_bytes - fine >= plan.total;
   }
   bool wanted(const qe_options* o, double eta) const {
-    return possible && (o->precond == QE_PC_MULTIGRID || eta <= mg_eta(plan.pc[0].nx * (long)plan.pc[0].ny * plan.pc[0].nz));
+    const char* v = getenv("QE_MG_ETA");   // overrides the threshold for every mesh
+    const double most = v ? atof(v) : large() ? kMgEtaLarge : kMgEta;
+    return possible && (o->precond == QE_PC_MULTIGRID || slow || eta <= most);
   }
   qe_status setup(Context& fine, const Charge& ch) {
     for (int l = 1; l < plan.nlev; ++l) {
@@ -1447,12 +1459,21 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
     eta = std::max(eta, 0.5 * o->newton_atol / nrm);
     eta = std::min(eta, o->krylov_rtol_max);
     eta = std::max(eta, mixed ? 1e-6 : 1e-13);
-    const bool use_mg = mg.wanted(o, eta);
+    bool use_mg = mg.wanted(o, eta);
+    qe_status s2;
+    const int trial = use_mg ? 0 : mg.trial(o);
+    if (trial > 0) {
+      if ((s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, trial, check, &pst, &its)) != QE_OK) return finish(s2, r, rep);
+      r.krylov_iters += its;
+      use_mg = mg.slow = pst == PCG_MAXIT;
+    }
     if (use_mg && (st = mg.prepare(cx, ch, phi)) != QE_OK) return finish(st, r, rep);
-    qe_status s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, o->krylov_maxit, check, &pst, &its,
-                          use_mg ? &mg.run : nullptr);
-    if (s2 != QE_OK) return finish(s2, r, rep);
-    r.krylov_iters += its;
+    if (use_mg || trial == 0) {
+      if ((s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, o->krylov_maxit, check, &pst, &its,
+                       use_mg ? &mg.run : nullptr)) != QE_OK)
+        return finish(s2, r, rep);
+      r.krylov_iters += its;
+    }
     if (use_mg) {
       r.mg_krylov_iters += its;
       r.mg_levels = mg.plan.nlev;
