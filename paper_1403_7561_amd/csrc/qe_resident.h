@@ -58,6 +58,7 @@ struct ResArgs {
   unsigned int* ticket;      // the next ticket; zeroed by the launch, like abort
   unsigned long long* abort; // set when a wait ran out
   Charge ch;
+  Quantum qm;                // eigenstates (one instance; n = 0: none)
   double atol, rtol_max, newton_rtol;
   int newton_maxit, ls_max, krylov_maxit;
   int lenient, init, apply, zero_free;

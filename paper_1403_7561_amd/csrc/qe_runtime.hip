@@ -640,6 +640,7 @@ ResArgs Context::resident_args(const MarchArgs& a, const ResPlan& plan, const in
   R.ticket = u32(lay.counters) + 9;
   R.abort = reinterpret_cast<unsigned long long*>(ws + lay.flags) + 1;
   R.ch = a.ch;
+  R.qm = quantum;
   R.atol = a.atol;
   R.rtol_max = a.rtol_max;
   R.newton_rtol = a.newton_rtol;
@@ -1349,7 +1350,9 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
     }
     linear = r.seq_levels == 0;
   }
-  if (march) {
+  // with eigenstates the resident solve alone (the march has no states)
+  const bool states = !mixed && !mg.possible && cx.sheets.n == 0 && cx.quantum.n > 0;
+  if (march || states) {
     MarchArgs a = cx.march_args(ch, o, phi, newton_rtol);
     a.init = linear ? MARCH_LINEAR : MARCH_INITIAL;
     a.apply = 1;
@@ -1374,7 +1377,7 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       if ((st = launch_resident(cx.s, ra, &plan, 1, wgs)) != QE_OK) return finish(st, r, rep);
       if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
     }
-    if (S.phase != MARCH_DONE) {
+    if (S.phase != MARCH_DONE && march) {
       // no cut fits, or the workgroups did not get the chip to themselves
       // (phi is then as it was)
       a.flags = const_cast<int*>(flags);
@@ -1384,34 +1387,36 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       if ((st = march_run(cx.s, a, hm, cx.events, o->check_every)) != QE_OK) return finish(st, r, rep);
       if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
     }
-    if (S.flags) return finish(Context::flag_error(S.flags), r, rep);
-    if (linear) r.init_krylov_iters = S.init_kry;
-    r.krylov_iters += S.kry;
-    r.newton_iters = S.newton;
-    r.ls_halvings = S.halv;
-    r.n_residual_evals = S.nres;
-    r.res0 = S.res0;
-    r.res_final = S.nrm;
-    const char* cg = "";
-    switch (S.status) {
-      case QE_ERR_NOT_CONVERGED:
-        st = fail(QE_ERR_NOT_CONVERGED, "Newton did not reach atol %.3e in %d steps (||F|| = %.3e)", o->newton_atol,
-                  o->newton_maxit, S.nrm);
-        break;
-      case QE_ERR_LINESEARCH:
-        st = fail(QE_ERR_LINESEARCH, "line search failed at Newton step %d (||F|| = %.3e)", S.newton, S.nrm);
-        break;
-      case QE_ERR_NONFINITE:
-      case QE_ERR_KRYLOV_BREAKDOWN:
-        cg = S.stage == MARCH_LINEAR ? "linear initial guess" : S.stage == MARCH_INITIAL ? "initial guess" : "Newton step";
-        st = S.stage == MARCH_NEWTON || S.why > PCG_CONVERGED
-                 ? fail((qe_status)S.status, "%s %d: CG failed (status %d)", cg, S.newton, S.why)
-                 : fail((qe_status)S.status, "residual not finite at the %s", cg);
-        break;
-      default:
-        st = (qe_status)S.status;
+    if (march || S.phase == MARCH_DONE) {
+      if (S.flags) return finish(Context::flag_error(S.flags), r, rep);
+      if (linear) r.init_krylov_iters = S.init_kry;
+      r.krylov_iters += S.kry;
+      r.newton_iters = S.newton;
+      r.ls_halvings = S.halv;
+      r.n_residual_evals = S.nres;
+      r.res0 = S.res0;
+      r.res_final = S.nrm;
+      const char* cg = "";
+      switch (S.status) {
+        case QE_ERR_NOT_CONVERGED:
+          st = fail(QE_ERR_NOT_CONVERGED, "Newton did not reach atol %.3e in %d steps (||F|| = %.3e)", o->newton_atol,
+                    o->newton_maxit, S.nrm);
+          break;
+        case QE_ERR_LINESEARCH:
+          st = fail(QE_ERR_LINESEARCH, "line search failed at Newton step %d (||F|| = %.3e)", S.newton, S.nrm);
+          break;
+        case QE_ERR_NONFINITE:
+        case QE_ERR_KRYLOV_BREAKDOWN:
+          cg = S.stage == MARCH_LINEAR ? "linear initial guess" : S.stage == MARCH_INITIAL ? "initial guess" : "Newton step";
+          st = S.stage == MARCH_NEWTON || S.why > PCG_CONVERGED
+                   ? fail((qe_status)S.status, "%s %d: CG failed (status %d)", cg, S.newton, S.why)
+                   : fail((qe_status)S.status, "residual not finite at the %s", cg);
+          break;
+        default:
+          st = (qe_status)S.status;
+      }
+      return finish(st, r, rep);
     }
-    return finish(st, r, rep);
   }
   if ((st = cx.stage(phi, 1, linear ? 1 : 0)) != QE_OK) return finish(st, r, rep);
   if (mixed) {

@@ -847,20 +847,12 @@ __device__ __forceinline__ void jv_tile_hm(const Geom& g, const WaveTile& w, int
 // waves that see it as a halo get the same coefficients, zeros included (the
 // J.v of a wave reads the owner's coefficients where its own are nonzero).
 //
-// The |psi_i|^2 loads are buffer loads with one per-lane offset (the
-// element's first node; 8 N < 2^31 bytes, checked on the host) and scalar
-// layer, corner and state steps; the next state's eight loads are issued
-// before the current state is used, into the other of two register sets.
-__device__ __forceinline__ void pc_electrons(const Geom& g, const WaveTile& w, int L, const Quantum& qm,
-                                             unsigned int act, const double src[8], double nq[8],
-                                             double dnq[8]) {
-  const long b0 = w.n00 + w.sxy * L;
-  double u[8];
-  {
-    const long o[8] = {0, 1, g.nx, g.nx + 1, w.sxy, w.sxy + 1, w.sxy + g.nx, w.sxy + g.nx + 1};
-#pragma unroll
-    for (int k = 0; k < 8; ++k) u[k] = qm.phik[b0 + o[k]];
-  }
+// u: phi^(k) at the element's nodes.  load(i, s2) reads |psi_i|^2 there; the
+// next state's values are loaded before the current state's are used, into the
+// other of two register sets.
+template <typename Load>
+__device__ __forceinline__ void pc_states(const Quantum& qm, unsigned int act, const double src[8], double u[8],
+                                          const Load& load, double nq[8], double dnq[8]) {
   gauss_interp(u);
   bool fast = qm.fast != 0;
 #pragma unroll
@@ -873,21 +865,6 @@ __device__ __forceinline__ void pc_electrons(const Geom& g, const WaveTile& w, i
     for (int q = 0; q < 8; ++q) u[q] = exp(-u[q]);   // e^-y_q
   }
   const bool all_fast = __builtin_amdgcn_ballot_w64(!fast) == 0;
-  const unsigned int vo = (unsigned int)(w.n00 * 8);
-  const unsigned int s0 = (unsigned int)(w.sxy * L * 8), sy = (unsigned int)(g.nx * 8),
-                     sz = (unsigned int)(w.sxy * 8);
-  const long nbytes = qm.N * 8;
-  auto load = [&](int i, double s2[8]) {
-    const __amdgpu_buffer_rsrc_t r = buf_res(qm.psi2 + qm.N * i, nbytes);
-    s2[0] = BufIO<double>::ld(r, vo, s0);
-    s2[1] = BufIO<double>::ld(r, vo + 8, s0);
-    s2[2] = BufIO<double>::ld(r, vo, s0 + sy);
-    s2[3] = BufIO<double>::ld(r, vo + 8, s0 + sy);
-    s2[4] = BufIO<double>::ld(r, vo, s0 + sz);
-    s2[5] = BufIO<double>::ld(r, vo + 8, s0 + sz);
-    s2[6] = BufIO<double>::ld(r, vo, s0 + sz + sy);
-    s2[7] = BufIO<double>::ld(r, vo + 8, s0 + sz + sy);
-  };
   // G = 1/(1 + t), t = e^-x in [e^-600, e^600]: a reciprocal refined twice
   // by Newton's iteration; dG/dx = t G^2 = G (t G), in that order so that it
   // does not underflow; P and 1/kT are applied after the sum.  Written with
@@ -960,6 +937,37 @@ __device__ __forceinline__ void pc_electrons(const Geom& g, const WaveTile& w, i
     nq[q] *= qm.pref;
     dnq[q] *= qm.pref * qm.inv_kT;
   }
+}
+
+// The same for a wave tile's element of layer L: the |psi_i|^2 loads are buffer
+// loads with one per-lane offset (the element's first node; 8 N < 2^31 bytes,
+// checked on the host) and scalar layer, corner and state steps.
+__device__ __forceinline__ void pc_electrons(const Geom& g, const WaveTile& w, int L, const Quantum& qm,
+                                             unsigned int act, const double src[8], double nq[8],
+                                             double dnq[8]) {
+  const long b0 = w.n00 + w.sxy * L;
+  double u[8];
+  {
+    const long o[8] = {0, 1, g.nx, g.nx + 1, w.sxy, w.sxy + 1, w.sxy + g.nx, w.sxy + g.nx + 1};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) u[k] = qm.phik[b0 + o[k]];
+  }
+  const unsigned int vo = (unsigned int)(w.n00 * 8);
+  const unsigned int s0 = (unsigned int)(w.sxy * L * 8), sy = (unsigned int)(g.nx * 8),
+                     sz = (unsigned int)(w.sxy * 8);
+  const long nbytes = qm.N * 8;
+  auto load = [&](int i, double s2[8]) {
+    const __amdgpu_buffer_rsrc_t r = buf_res(qm.psi2 + qm.N * i, nbytes);
+    s2[0] = BufIO<double>::ld(r, vo, s0);
+    s2[1] = BufIO<double>::ld(r, vo + 8, s0);
+    s2[2] = BufIO<double>::ld(r, vo, s0 + sy);
+    s2[3] = BufIO<double>::ld(r, vo + 8, s0 + sy);
+    s2[4] = BufIO<double>::ld(r, vo, s0 + sz);
+    s2[5] = BufIO<double>::ld(r, vo + 8, s0 + sz);
+    s2[6] = BufIO<double>::ld(r, vo, s0 + sz + sy);
+    s2[7] = BufIO<double>::ld(r, vo + 8, s0 + sz + sy);
+  };
+  pc_states(qm, act, src, u, load, nq, dnq);
 }
 
 // ---------------------------------------------------------------------------
