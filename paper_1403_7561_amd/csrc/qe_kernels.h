@@ -14,6 +14,10 @@ struct Box {
   __host__ __device__ bool contains(double x, double y, double z) const {
     return x >= x0 && x <= x1 && y >= y0 && y <= y1 && z >= z0 && z <= z1;
   }
+  // the same along one axis
+  __host__ __device__ bool spans(int axis, double v) const {
+    return axis == 0 ? v >= x0 && v <= x1 : axis == 1 ? v >= y0 && v <= y1 : v >= z0 && v <= z1;
+  }
 };
 
 struct BoxSet {
