@@ -1026,8 +1026,8 @@ static const long kMgMinNodes = 250000;
 static const long kMgMinCoarse = 2000;
 static const int kMgMaxLevels = 6;
 // AUTO: multigrid for CG tolerances at or below kMgEta on meshes of up to
-// kMgLargeNodes nodes and with eigenstates (whose coarse levels evaluate the
-// states too); on larger ones at or below kMgEtaLarge, and above it when a
+// kMgLargeNodes nodes (with eigenstates, whose coarse levels evaluate the
+// states too, kMgAddTopNodes, and without the trial); on larger ones at or below kMgEtaLarge, and above it when a
 // trial of kMgTrial iterations with Jacobi alone does not suffice, then for
 // the rest of the solve.  A V-cycle costs 4 to 7 Jacobi iterations and a solve
 // with it at the forcing term's cap of 0.3 takes 4 or 5; Jacobi takes 5 to 100
@@ -1037,9 +1037,8 @@ static const int kMgMaxLevels = 6;
 // 12.4, with Robin gates 23.6 / 21.8 / 19.3 / 19.5; at 200x160x81 37.1 / 33.3 /
 // 27.0 / 26.6; full charge at 145x129x73 17.1 / 15.2 / 20.2 / 16.2; junctions
 // of 366,000 and 1,010,000 nodes 20.9 / 19.0 / 14.0 / 13.5 and 50.5 / 42.4 /
-// 24.8 / 25.3; FP64 at 257x200x81 71.5 / 63.9 / 32.1 / 34.6; mixed at 257x257x129
-// 93.1 / 53.7 / 39.2 / 41.3.  A trial of 20 or 30 iterations: 12.7 / 13.0 at
-// 129x129x65, 15.2 / 15.2 for the full charge.  Below the line: 91x89x35 8.4 /
+// 24.8 / 25.3; FP64 at 257x200x81 71.5 / 63.9 / 32.1 / 34.6.  A trial of 20 or 30
+// iterations: 12.7 / 13.0 at 129x129x65, 15.2 / 15.2 for the full charge.  Below the line: 91x89x35 8.4 /
 // 8.3 / 9.2 / 8.9; with 16 states at 97x97x49 12.1 / 12.1 / 13.1 / 13.4.
 static const double kMgEta = 3e-2, kMgEtaLarge = 1e-1;
 static const long kMgLargeNodes = 350000;
@@ -1167,6 +1166,12 @@ struct MgState {
   char* base = nullptr;
   bool possible = false, ready = false;
   bool slow = false;   // a trial with Jacobi alone ran out
+  // The coarse start of a finer mesh keeps kMgEta (below kMgAddTopNodes) and
+  // has no trial: it is solved to a few digits only, and with the larger meshes' rule on it the 257x257x129 solves
+  // of five inputs took 37.8 / 41.9 / 44.1 / 35.2 / 39.0 ms, without 36.4 / 37.0 /
+  // 44.2 / 34.5 / 43.0 (with 1e-1 and no trial on the fine mesh 36.7 / 37.3 /
+  // 60.2 / 34.8 / 60.2).
+  bool start = false;
   Context cx[kMgMaxLevels];   // levels 1 .. nlev - 1
   MgGrid lv[kMgMaxLevels];
   MgRun run{};
@@ -1175,13 +1180,15 @@ struct MgState {
 
   bool large() const {
     const qe_problem& p = plan.pc[0];
-    return !p.quantum && (long)p.nx * p.ny * p.nz >= env_long("QE_MG_LARGE_NODES", kMgLargeNodes);
+    const long most = start || p.quantum ? env_long("QE_MG_ADD_NODES", kMgAddTopNodes)
+                                         : env_long("QE_MG_LARGE_NODES", kMgLargeNodes);
+    return (long)p.nx * p.ny * p.nz >= most;
   }
   // Iterations that a Newton step's CG is tried with Jacobi alone before
   // multigrid takes it (0: no trial).
   int trial(const qe_options* o) const {
     const int most = env_int("QE_MG_TRIAL", kMgTrial);
-    return possible && large() && !slow && o->precond == QE_PC_AUTO && most < o->krylov_maxit ? most : 0;
+    return possible && large() && !start && !plan.pc[0].quantum && !slow && o->precond == QE_PC_AUTO && most < o->krylov_maxit ? most : 0;
   }
 
   // Whether multigrid can serve this call (an allocating entry point, a
@@ -1306,6 +1313,7 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
   const bool mixed = o->precision == QE_PREC_MIXED;
   MgState mg;
   mg.plan_for(p, o, ws, ws_bytes, mixed, no_alloc);
+  mg.start = trusted;
   // FP64 with Jacobi alone marches on the device; the host drives the solves
   // with multigrid, sheets or eigenstates and the FP32 CG
   const bool march = !mixed && !mg.possible && cx.sheets.n == 0 && cx.quantum.n == 0;
