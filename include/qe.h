@@ -39,7 +39,7 @@
  *    return unspecified.  Concurrent calls must not share a workspace.
  *  - `stream` is a hipStream_t passed as void* (NULL = default stream).  All
  *    device work is enqueued on it; every entry point returns after
- *    synchronising that stream (the Newton decisions are taken on the host).
+ *    synchronising that stream.
  *  - Errors never abort: a negative qe_status is returned and
  *    qe_last_error() describes it.  Invalid arguments are detected before any
  *    device work is enqueued, except the device-array checks (eps_r > 0,
@@ -98,10 +98,10 @@ typedef enum {
  * more the finest level only adds its correction (z = S r + P B_1 P^T r).
  * It is symmetric positive definite (any weight below 2 keeps it so), so
  * the CG stays plain CG.  AUTO takes multigrid for the Newton steps whose
- * CG tolerance is at most 3e-2 (1e-1 on meshes of 4M nodes and more, where
- * a V-cycle costs less relative to a Jacobi iteration) and for the adjoint,
- * where one V-cycle saves more iterations than it costs, and Jacobi
- * otherwise.  In mixed precision the
+ * CG tolerance is at most 3e-2 (1e-1 on meshes of 350000 nodes and more
+ * without eigenstates; there the others too, once 12 Jacobi iterations did
+ * not finish one) and for the adjoint, where one V-cycle saves more
+ * iterations than it costs, and Jacobi otherwise.  In mixed precision the
  * V-cycle runs in FP32 like the CG it serves.  With sheets the V-cycle
  * leaves out the Robin face term (it stays positive definite); with
  * eigenstates every coarse mesh carries them, injected like the potential.
@@ -340,18 +340,19 @@ qe_status qe_adjoint(const qe_problem* p, const qe_physics* ph, const qe_options
                      double* dQ_deps, double* lam, void* ws, size_t ws_bytes,
                      void* stream, qe_report* rep);
 
-/* Batched solve of many independent devices in one persistent launch: the
+/* Batched solve of many independent devices in the same launches: the
  * design searches of Sec. IV run many device simulations at once (gate
  * voltages varied as parameters, many layouts side by side, each device the
  * nonlinear Poisson problem of Sec. II.A), which here becomes a gate-voltage
  * sweep over uneven meshes on one GPU.  Newton, line search and CG run on
  * the device for every instance, with the same algorithm and stopping rules
- * as qe_solve.
+ * as qe_solve from the linear guess.
  *   probs: host [n_inst] of qe_problem (device arrays inside);
  *   phi: host [n_inst] of device pointers, each [N_k]; out: solutions;
  *   boxes: host [n_boxes][6]; counts: host [n_inst][n_boxes] (may be NULL
  *     when n_boxes = 0);
- *   tune_cache: path of the autotuner's cache file (NULL = no cache);
+ *   tune_cache: path of a file that records the launch shape chosen for a set
+ *     of mesh sizes (NULL = none);
  *   reps: host [n_inst] or NULL.
  * All instances share ph and o; o->precision must be FP64. */
 size_t qe_batch_workspace_bytes(int32_t n_inst, const qe_problem* probs, const qe_options* o);
@@ -416,8 +417,8 @@ size_t qe_schrodinger_workspace_bytes(const qe_problem* p, int32_t n_states);
 
 /* Lowest n_states (1 .. QE_MAX_EIG) eigenpairs by block LOBPCG (Knyazev's
  * locally optimal block preconditioned CG) on H - sigma M with sigma below
- * every V (so the operator is SPD), two guard vectors, the Jacobi
- * preconditioner, soft locking of converged vectors, and Rayleigh-Ritz on
+ * every V (so the operator is SPD), two guard vectors, a
+ * Chebyshev-Jacobi preconditioner, soft locking of converged vectors, and Rayleigh-Ritz on
  * the block [X, W, P] (Gram matrices on the GPU; the small dense generalized
  * eigenproblem on the host).  Operators use the wave-tiled J.v.
  * The iteration runs on the bounding box of the free nodes grown by one
