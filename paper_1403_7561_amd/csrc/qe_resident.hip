@@ -39,10 +39,11 @@
 // not finished, and the host takes the tick-by-tick march instead.
 //
 // Measured, whole solves, with the host-driven launches of one kernel per CG
-// step / the march / resident: 17x17x9 3.2 / 1.6 / 0.84 ms, 33x29x41 9.8 / 5.6
-// / 3.1, 65x65x33 7.1 / 5.0 / 3.1; 256 instances of 25 to 52 thousand nodes 505
-// / 251 / 245.  A CG iteration at 65x65x33 in 180 boxes takes ~6 us: product
-// and updates 2.9, sums of the workgroup 1, waiting 2, sums of all 0.4.
+// step / the march / resident: 17x17x9 3.2 / 2.5 / 0.85 ms, a junction of
+// 33x29x41 10.9 / 10.7 / 3.3, 65x65x33 7.2 / 6.4 / 3.1; 256 instances of 33x33x17
+// to 65x65x33 in one call 505 / 251 / 245.  A CG iteration at 65x65x33 in 169
+// boxes takes ~6 us: product and updates 1.9, sums of the workgroup 0.9,
+// publishing 0.5, waiting 2.6, sums of all 0.5.
 #include <algorithm>
 #include <vector>
 
