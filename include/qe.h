@@ -101,7 +101,9 @@ typedef enum {
  * CG tolerance is at most 3e-2 (1e-1 on meshes of 350000 nodes and more
  * without eigenstates; there the others too, once 12 Jacobi iterations did
  * not finish one) and for the adjoint, where one V-cycle saves more
- * iterations than it costs, and Jacobi otherwise.  In mixed precision the
+ * iterations than it costs, and Jacobi otherwise.  A V-cycle step that the
+ * line search refuses at full length while its linear residual exceeds half of
+ * ||F|| is solved again to a tenth of its tolerance.  In mixed precision the
  * V-cycle runs in FP32 like the CG it serves.  With sheets the V-cycle
  * leaves out the Robin face term (it stays positive definite); with
  * eigenstates every coarse mesh carries them, injected like the potential.

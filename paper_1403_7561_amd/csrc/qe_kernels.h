@@ -155,6 +155,10 @@ void launch_cg_jv32(hipStream_t s, const Geom& g, const WaveMap& wm, int cgblock
 // After an FP64 CG loop: the last iteration's x += alpha p (none after a
 // breakdown).
 void launch_cg_finish_x64(hipStream_t s, int nblocks, long N, const PcgCtx* ctx, const double* p, double* x);
+// Squared norm over the free nodes of v64 or, when that is NULL, v32 (partials
+// of nblocks blocks, then one sum).
+void launch_free_norm2(hipStream_t s, int nblocks, long N, const uint8_t* mask, const double* v64, const float* v32,
+                       double* partial, double* out);
 // FP32 tile-major permittivity for the wave-tiled J.v (see tile_slot).
 void launch_stage_eps32(hipStream_t s, int nblocks, const Geom& g, const double* eps, float* eps_t, long nslots);
 // Count of real elements with a set tile-major flag, added to *out.

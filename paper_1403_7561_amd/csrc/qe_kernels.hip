@@ -870,6 +870,20 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_finish_x(long N, const PcgCt
     x[n] += alpha * p[n];
 }
 
+// Partials of the squared norm over the free nodes.
+template <typename T>
+__global__ __launch_bounds__(kVecThreads) void k_free_norm2(long N, const uint8_t* __restrict__ mask,
+                                                           const T* __restrict__ v, double* __restrict__ part) {
+  __shared__ double sred[kVecThreads / 64];
+  double a = 0.0;
+  for (long n = (long)blockIdx.x * kVecThreads + threadIdx.x; n < N; n += (long)gridDim.x * kVecThreads) {
+    const double u = mask[n] ? 0.0 : (double)v[n];
+    a += u * u;
+  }
+  const double t = block_sum(a, sred);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
 // One block: sum of n partials (fixed order) into *out.
 __global__ __launch_bounds__(kVecThreads) void k_sum_partials(const double* __restrict__ part, int n,
                                                              double* __restrict__ out) {
@@ -1089,6 +1103,15 @@ void launch_cg_jv32(hipStream_t s, const Geom& g, const WaveMap& wm, int cgblock
                     PcgCtx* ctx, CgProgress* prog, const double* part_rz, double* part_py) {
   QE_LAUNCH(k_cg_jv<float>, wm.nblocks, 256, s, g, wm, eps_t, cbits, cq, z, y, p, x, k, ctx, prog, part_rz, cgblocks,
             part_py);
+}
+
+void launch_free_norm2(hipStream_t s, int nblocks, long N, const uint8_t* mask, const double* v64, const float* v32,
+                       double* partial, double* out) {
+  if (v64)
+    QE_LAUNCH((k_free_norm2<double>), nblocks, kVecThreads, s, N, mask, v64, partial);
+  else
+    QE_LAUNCH((k_free_norm2<float>), nblocks, kVecThreads, s, N, mask, v32, partial);
+  QE_LAUNCH(k_sum_partials, 1, kVecThreads, s, partial, nblocks, out);
 }
 
 void launch_stage_eps32(hipStream_t s, int nblocks, const Geom& g, const double* eps, float* eps_t, long nslots) {

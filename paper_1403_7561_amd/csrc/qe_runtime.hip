@@ -554,6 +554,15 @@ qe_status Context::residual(const Charge& ch, const double* phi, const double* d
   return QE_OK;
 }
 
+qe_status Context::free_norm2(const double* v64, const float* v32, double* norm2_host) {
+  launch_free_norm2(s, vblocks, N, u8(lay.mask), v64, v32, f64(lay.partial), f64(lay.scal));
+  QE_HIP(hipGetLastError());
+  QE_HIP(hipMemcpyAsync(hm->scal, ws + lay.scal, sizeof(double), hipMemcpyDeviceToHost, s));
+  QE_HIP(hipStreamSynchronize(s));
+  *norm2_host = hm->scal[0];
+  return QE_OK;
+}
+
 #ifndef QE_CG_EVENT_EVERY
 #define QE_CG_EVENT_EVERY 8
 #endif
@@ -1043,6 +1052,15 @@ static const int kMgMaxLevels = 6;
 static const double kMgEta = 3e-2, kMgEtaLarge = 1e-1;
 static const long kMgLargeNodes = 350000;
 static const int kMgTrial = 12;
+// The CG stops in the norm (r^T B r)^(1/2) of its preconditioner B.  The
+// V-cycle's weighs the smooth part of r far more than ||F||, in which the line
+// search measures: at a loose tolerance a step may leave ||F + J x|| above
+// ||F||, and then no length of it need go down (a 257x257x129 stack in mixed
+// precision stopped in the line search for 19 of 1169 inputs, with tolerances
+// of 0.1 to 0.3, and crept with up to 1367 halvings for others; with the check
+// none does and the mean solve takes 40.3 instead of 43.0 ms).  Below this fraction of ||F|| it does go down; Jacobi's norm
+// differs from it only by the spread of the diagonal.
+static const double kMgForcing = 0.5;
 // Smoothing steps on the coarsest mesh (at 129x129x65 with the weight below,
 // 2 / 4 / 6 gave 37 / 30 / 28 adjoint iterations in 7.6 / 6.9 / 6.9 ms and
 // solves of 12.0 / 11.0 / 11.3 ms; a fifth level, down to 9x9x5, measured
@@ -1460,6 +1478,10 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
   r.res0 = nrm;
   r.res_final = nrm;
   if (!std::isfinite(nrm)) return finish(fail(QE_ERR_NONFINITE, "residual not finite at the initial guess"), r, rep);
+  auto cg_failed = [&](int it) {
+    return fail(pst == PCG_BREAKDOWN ? QE_ERR_KRYLOV_BREAKDOWN : QE_ERR_NONFINITE, "Newton step %d: CG failed (status %d)",
+                it, pst);
+  };
   st = QE_ERR_NOT_CONVERGED;
   for (int it = 0; it <= o->newton_maxit; ++it) {
     if (nrm <= o->newton_atol || nrm <= newton_rtol * r.res0) {
@@ -1471,7 +1493,8 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
                           : std::min(o->krylov_rtol_max, QE_EW_GAMMA * (nrm / prev) * (nrm / prev));
     eta = std::max(eta, 0.5 * o->newton_atol / nrm);
     eta = std::min(eta, o->krylov_rtol_max);
-    eta = std::max(eta, mixed ? 1e-6 : 1e-13);
+    const double eta_min = mixed ? 1e-6 : 1e-13;
+    eta = std::max(eta, eta_min);
     bool use_mg = mg.wanted(o, eta);
     qe_status s2;
     const int trial = use_mg ? 0 : mg.trial(o);
@@ -1491,9 +1514,9 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       r.mg_krylov_iters += its;
       r.mg_levels = mg.plan.nlev;
     }
+    int left = o->krylov_maxit - its;   // of this linear system
     if (pst == PCG_BREAKDOWN || pst == PCG_NONFINITE) {
-      st = fail(pst == PCG_BREAKDOWN ? QE_ERR_KRYLOV_BREAKDOWN : QE_ERR_NONFINITE, "Newton step %d: CG failed (status %d)",
-                it, pst);
+      st = cg_failed(it);
       break;
     }
     double lam = 1.0, nt = 0.0;
@@ -1508,8 +1531,32 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
         ok = true;
         break;
       }
+      // a full V-cycle step that is refused: was it solved far enough to go
+      // down (kMgForcing)?  If not, the same system again to a tenth.
+      if (hv == 0 && use_mg && pst == PCG_CONVERGED && eta > eta_min && left > 0) {
+        if ((s2 = cx.free_norm2(mixed ? nullptr : cx.f64(cx.lay.r), mixed ? cx.f32(cx.lay.r32) : nullptr, &n2)) != QE_OK)
+          return finish(s2, r, rep);
+        if (!(std::sqrt(n2) <= kMgForcing * nrm)) {
+          eta = std::max(0.1 * eta, eta_min);
+          // (the residual at the refused point overwrote F and J)
+          if ((s2 = cx.residual(ch, phi, nullptr, nullptr, 0.0, mixed, nullptr, nullptr)) != QE_OK ||
+              (s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, left, check, &pst, &its, &mg.run)) != QE_OK)
+            return finish(s2, r, rep);
+          r.n_residual_evals++;
+          r.krylov_iters += its;
+          r.mg_krylov_iters += its;
+          left -= its;
+          if (pst == PCG_BREAKDOWN || pst == PCG_NONFINITE) break;
+          hv = -1;
+          continue;
+        }
+      }
       lam *= 0.5;
       r.ls_halvings++;
+    }
+    if (pst == PCG_BREAKDOWN || pst == PCG_NONFINITE) {
+      st = cg_failed(it);
+      break;
     }
     if (!ok) {
       st = fail(QE_ERR_LINESEARCH, "line search failed at Newton step %d (||F|| = %.3e)", it, nrm);

@@ -1,0 +1,31 @@
+"""Newton steps solved with the V-cycle to a loose tolerance.  The CG stops in
+its preconditioner's norm; for these inputs (rough 257x257x129 stacks) a step
+of 0.1 to 0.3 in that norm left ||F + J x|| above ||F||, and the line search
+ended the solve (-5) or crept to the iteration limit.
+
+Potentials against the solve with Jacobi alone: both stop at ||F|| <= 1e-9, and
+the smallest eigenvalue of J is above 11.7 h (pi h / (2 L))^2 = 3e-4 (h = 0.78,
+L = 100 nm, the depth of the stack), so they differ by less than 2e-9 / 3e-4 =
+7e-6 in norm over 8.5 million nodes of mostly 0.1 V and more; 1e-6 of the
+largest is the standing tolerance in mixed precision."""
+import pytest
+
+from paper_1403_7561_amd import qe
+from perf import cases
+
+pytestmark = pytest.mark.gpu
+
+CASE = {"kind": "solve", "nx": 257, "ny": 257, "nz": 129, "stat": "fd", "T": 4.0, "precision": "mixed", "rough": True}
+
+
+@pytest.mark.parametrize("seed", [135, 251, 256])
+def test_loose_steps_go_down(seed):
+    s = cases.prepare(CASE, seed)
+    opts = s["opts"]
+    phi, _, rep = qe.qe_solve(s["prob"], opts=opts, ws=s["ws"])
+    assert rep["res_final"] <= opts.newton_atol and rep["mg_krylov_iters"] > 0
+    assert rep["newton_iters"] <= 20 and rep["ls_halvings"] <= 10
+    opts.precond = 1
+    ref, _, rep = qe.qe_solve(s["prob"], opts=opts, ws=s["ws"])
+    assert rep["mg_krylov_iters"] == 0
+    assert float((phi - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
