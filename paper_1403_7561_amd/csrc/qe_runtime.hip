@@ -1503,7 +1503,7 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       r.krylov_iters += its;
       use_mg = mg.slow = pst == PCG_MAXIT;
     }
-    if (use_mg && (st = mg.prepare(cx, ch, phi)) != QE_OK) return finish(st, r, rep);
+    if (use_mg && (s2 = mg.prepare(cx, ch, phi)) != QE_OK) return finish(s2, r, rep);
     if (use_mg || trial == 0) {
       if ((s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, o->krylov_maxit, check, &pst, &its,
                        use_mg ? &mg.run : nullptr)) != QE_OK)

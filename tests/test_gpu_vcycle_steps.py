@@ -8,8 +8,10 @@ the smallest eigenvalue of J is above 11.7 h (pi h / (2 L))^2 = 3e-4 (h = 0.78,
 L = 100 nm, the depth of the stack), so they differ by less than 2e-9 / 3e-4 =
 7e-6 in norm over 8.5 million nodes of mostly 0.1 V and more; 1e-6 of the
 largest is the standing tolerance in mixed precision."""
+import numpy as np
 import pytest
 
+import synth
 from paper_1403_7561_amd import qe
 from perf import cases
 
@@ -29,3 +31,15 @@ def test_loose_steps_go_down(seed):
     ref, _, rep = qe.qe_solve(s["prob"], opts=opts, ws=s["ws"])
     assert rep["mg_krylov_iters"] == 0
     assert float((phi - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_iteration_limit_is_reported(monkeypatch, precision):
+    """newton_maxit reached with the V-cycle: QE_ERR_NOT_CONVERGED, not QE_OK"""
+    monkeypatch.setenv("QE_MG_MIN_NODES", "1000")
+    monkeypatch.setenv("QE_MG_MIN_COARSE", "300")
+    P = qe.Problem(synth.double_dot_device("t", 36, 30, 20, np.array([1.5, 1.4, 0.5, 0.7, 0.3])))
+    opts = qe.qe_default_options(newton_atol=1e-10, newton_maxit=2, precision=precision, precond=2)
+    _, _, rep = qe.qe_solve(P, opts=opts, check=False)
+    assert rep["mg_krylov_iters"] > 0 and rep["newton_iters"] == 2 and rep["res_final"] > 1e-10
+    assert rep["status"] == -4
