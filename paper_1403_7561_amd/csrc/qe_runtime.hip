@@ -1498,23 +1498,24 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
     bool use_mg = mg.wanted(o, eta);
     qe_status s2;
     const int trial = use_mg ? 0 : mg.trial(o);
+    int left = o->krylov_maxit;   // iterations of this linear system
     if (trial > 0) {
       if ((s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, trial, check, &pst, &its)) != QE_OK) return finish(s2, r, rep);
       r.krylov_iters += its;
+      left -= its;
       use_mg = mg.slow = pst == PCG_MAXIT;
     }
     if (use_mg && (s2 = mg.prepare(cx, ch, phi)) != QE_OK) return finish(s2, r, rep);
     if (use_mg || trial == 0) {
-      if ((s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, o->krylov_maxit, check, &pst, &its,
-                       use_mg ? &mg.run : nullptr)) != QE_OK)
+      if ((s2 = cx.pcg(mixed, cx.f64(cx.lay.F), -1.0, eta, left, check, &pst, &its, use_mg ? &mg.run : nullptr)) != QE_OK)
         return finish(s2, r, rep);
       r.krylov_iters += its;
+      left -= its;
     }
     if (use_mg) {
       r.mg_krylov_iters += its;
       r.mg_levels = mg.plan.nlev;
     }
-    int left = o->krylov_maxit - its;   // of this linear system
     if (pst == PCG_BREAKDOWN || pst == PCG_NONFINITE) {
       st = cg_failed(it);
       break;

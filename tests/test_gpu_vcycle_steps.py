@@ -43,3 +43,16 @@ def test_iteration_limit_is_reported(monkeypatch, precision):
     _, _, rep = qe.qe_solve(P, opts=opts, check=False)
     assert rep["mg_krylov_iters"] > 0 and rep["newton_iters"] == 2 and rep["res_final"] > 1e-10
     assert rep["status"] == -4
+
+
+def test_iteration_limit_above_the_trial(monkeypatch):
+    """krylov_maxit just above the trial's length: the trial's iterations
+    count, so a Newton step takes no more than the limit in all"""
+    monkeypatch.setenv("QE_MG_MIN_NODES", "1000")
+    monkeypatch.setenv("QE_MG_LARGE_NODES", "1000")
+    monkeypatch.setenv("QE_MG_TRIAL", "2")
+    P = qe.Problem(synth.double_dot_device("t", 36, 30, 20, np.array([1.5, 1.4, 0.5, 0.7, 0.3])))
+    opts = qe.qe_default_options(newton_atol=1e-10, newton_maxit=1, krylov_maxit=3, init_guess=0)
+    _, _, rep = qe.qe_solve(P, opts=opts, check=False)
+    assert rep["mg_krylov_iters"] > 0                # the trial ran out
+    assert rep["krylov_iters"] - rep["init_krylov_iters"] <= 3 * rep["newton_iters"]
