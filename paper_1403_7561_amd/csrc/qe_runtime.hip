@@ -1205,7 +1205,7 @@ struct MgState {
   // Iterations that a Newton step's CG is tried with Jacobi alone before
   // multigrid takes it (0: no trial).
   int trial(const qe_options* o) const {
-    const int most = env_int("QE_MG_TRIAL", kMgTrial);
+    const int most = std::max(0, env_int("QE_MG_TRIAL", kMgTrial));
     return possible && large() && !start && !plan.pc[0].quantum && !slow && o->precond == QE_PC_AUTO && most < o->krylov_maxit ? most : 0;
   }
 

@@ -56,3 +56,16 @@ def test_iteration_limit_above_the_trial(monkeypatch):
     _, _, rep = qe.qe_solve(P, opts=opts, check=False)
     assert rep["mg_krylov_iters"] > 0                # the trial ran out
     assert rep["krylov_iters"] - rep["init_krylov_iters"] <= 3 * rep["newton_iters"]
+
+
+def test_negative_trial_is_none(monkeypatch):
+    """a trial length below 0 is no trial: the CG still runs"""
+    monkeypatch.setenv("QE_MG_MIN_NODES", "1000")
+    monkeypatch.setenv("QE_MG_LARGE_NODES", "1000")
+    P = qe.Problem(synth.double_dot_device("t", 36, 30, 20, np.array([1.5, 1.4, 0.5, 0.7, 0.3])))
+    opts = qe.qe_default_options(newton_atol=1e-10)
+    monkeypatch.setenv("QE_MG_TRIAL", "0")
+    ref, _, rref = qe.qe_solve(P, opts=opts)
+    monkeypatch.setenv("QE_MG_TRIAL", "-1")
+    phi, _, rep = qe.qe_solve(P, opts=opts, check=False)
+    assert rep == rref and bool((phi == ref).all())
