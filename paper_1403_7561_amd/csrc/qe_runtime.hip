@@ -1221,9 +1221,10 @@ struct MgState {
     possible = mg_plan(p, base, plan) && ws_bytes - fine >= plan.total;
   }
   bool wanted(const qe_options* o, double eta) const {
+    if (!possible) return false;
     const char* v = getenv("QE_MG_ETA");   // overrides the threshold for every mesh
     const double most = v ? atof(v) : large() ? kMgEtaLarge : kMgEta;
-    return possible && (o->precond == QE_PC_MULTIGRID || slow || eta <= most);
+    return o->precond == QE_PC_MULTIGRID || slow || eta <= most;
   }
   qe_status setup(Context& fine, const Charge& ch) {
     for (int l = 1; l < plan.nlev; ++l) {
