@@ -140,12 +140,15 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
   __shared__ int s_ticket;
   const int t = threadIdx.x, wave = t >> 6;
   unsigned int epoch = 0;   // exchanges of the instance so far; their tags are 1, 2, ...
+  // The abort word is read by one thread for the workgroup: another workgroup
+  // may set it at any time, and waves that read it apart could part ways.
   if (t == 0) {
-    s_dead = 0;
+    s_dead = agent_load(A.abort) != 0u ? 1 : 0;
     s_ch = A.ch;
     if constexpr (kQ) s_qm = A.qm;
   }
-  if (agent_load(A.abort) != 0u) return;
+  __syncthreads();
+  if (s_dead) return;
 
   // After a poll: whether the wave's wait is over (everything `here`, or the
   // wait ran out and s_dead is set); k counts the polls.
@@ -170,7 +173,10 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
       I = A.one;
     } else {
       __syncthreads();
-      if (t == 0) s_ticket = (int)__hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (t == 0)   // (after an abort none is taken)
+        s_ticket = agent_load(A.abort) != 0u
+                       ? A.n_seats
+                       : (int)__hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __syncthreads();
       const int k = __builtin_amdgcn_readfirstlane(s_ticket);
       if (k >= A.n_seats) return;
