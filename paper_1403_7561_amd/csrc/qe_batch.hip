@@ -394,6 +394,7 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
     R.dir_id = p.dir_id;
     R.dir_val = p.dir_val;
     R.phi = phi[i];
+    R.keep = nullptr;   // (every start is the linear guess)
     // two vectors' room each
     R.w0 = reinterpret_cast<unsigned long long*>(I.x);
     R.w1 = reinterpret_cast<unsigned long long*>(I.z);

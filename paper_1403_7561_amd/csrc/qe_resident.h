@@ -40,6 +40,7 @@ struct ResInst {
   const int32_t* dir_id;
   const double* dir_val;
   double* phi;
+  double* keep;             // [N] receives phi as it is before the solve; NULL: not needed
   // what neighbouring boxes read: two words per value, [2 N] each, in this
   // order one after the other
   unsigned long long *w0, *w1, *d;

@@ -36,7 +36,9 @@
 // one per compute unit, so on a device without other work they all run; when
 // other work keeps some out for too long, every wait ends after a bounded
 // number of polls, the workgroups leave, the instance's state says that it is
-// not finished, and the host takes the tick-by-tick march instead.
+// not finished, and the host takes the tick-by-tick march instead, from the
+// caller's phi: workgroups that had the last exchange in time have written
+// their part by then, so a warm start is kept and put back.
 //
 // Measured, whole solves, with the host-driven launches of one kernel per CG
 // step / the march / resident: 17x17x9 3.2 / 2.5 / 0.85 ms, a junction of
@@ -905,7 +907,7 @@ int resident_fit(size_t bytes, long nodes, int wgs) {
 
 // Zeroes the buffers between the boxes of every instance (w0, w1 and d are
 // six vectors that follow each other; then the part) and the launch's two
-// counters, and sets the state's phase.
+// counters, sets the state's phase, and keeps phi where that is asked for.
 __global__ __launch_bounds__(256) void k_resident_zero(ResArgs A) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     *A.ticket = 0u;
@@ -919,6 +921,8 @@ __global__ __launch_bounds__(256) void k_resident_zero(ResArgs A) {
     ulonglong2* const p = reinterpret_cast<ulonglong2*>(I.w0);
     const long words = reinterpret_cast<ulonglong2*>(I.d) - p + n;
     for (long i = t0; i < words; i += stride) p[i] = make_ulonglong2(0, 0);
+    if (I.keep)
+      for (long i = t0; i < n; i += stride) I.keep[i] = I.phi[i];
     ulonglong2* const q = reinterpret_cast<ulonglong2*>(I.part);
     for (long i = t0; i < (long)I.plan.nwg * 4 * kResCopies + n; i += stride) q[i] = make_ulonglong2(0, 0);
   }

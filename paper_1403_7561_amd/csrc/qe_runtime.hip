@@ -636,6 +636,7 @@ ResArgs Context::resident_args(const MarchArgs& a, const ResPlan& plan, const in
   I.dir_id = prob.dir_id;
   I.dir_val = prob.dir_val;
   I.phi = a.one.phi;
+  I.keep = a.init == MARCH_LINEAR ? nullptr : f64(lay.invdiag);   // (the resident solve's D^-1 is in registers)
   // two vectors' room each: F and x, r and p, y and z follow each other
   I.w0 = reinterpret_cast<unsigned long long*>(ws + lay.F);
   I.w1 = reinterpret_cast<unsigned long long*>(ws + lay.r);
@@ -1403,10 +1404,13 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       ResArgs ra = cx.resident_args(a, plan, flags);
       if ((st = launch_resident(cx.s, ra, &plan, 1, wgs)) != QE_OK) return finish(st, r, rep);
       if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
+      // Not finished: the workgroups did not get the chip to themselves.  Those
+      // that saw the last exchange in time have written their part of phi.
+      if (S.phase != MARCH_DONE && ra.one.keep &&
+          hipMemcpyAsync(phi, ra.one.keep, cx.N * sizeof(double), hipMemcpyDeviceToDevice, cx.s) != hipSuccess)
+        return finish(fail(QE_ERR_HIP, "copy of the initial potential failed"), r, rep);
     }
     if (S.phase != MARCH_DONE && march) {
-      // no cut fits, or the workgroups did not get the chip to themselves
-      // (phi is then as it was)
       a.flags = const_cast<int*>(flags);
       if (hm.prog) hm.prog->word = 0;
       a.prog = hm.prog_dev;
