@@ -59,7 +59,8 @@ namespace qe {
 // unit, and the others.  QE_RESIDENT_POLLS sets both (tests of the fallback).
 constexpr int kResPollsFirst = 20000, kResPollsLater = 2000000;
 
-// MarchState::phase of an instance one of whose workgroups gave up
+// MarchState::phase of an instance that is not finished: one of its workgroups
+// gave up, or all of them left it to the march
 constexpr int kResGaveUp = -1;
 
 typedef unsigned long long res_word;
@@ -742,6 +743,11 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
     int trial = 0;
     double nrm = 0.0, res0 = 0.0, prev = -1.0, lam = 1.0;
     bool step = false;
+    // This form of the CG takes p^T J p and J p from recurrences, which lose
+    // digits to cancellation where the direct form does not.  A CG that breaks
+    // down and a line search that fails are therefore not the last word: the
+    // instance is left unfinished, and the march solves it from its start.
+    bool handed = false;
     for (;;) {
       double n2;
       if (!residual(stage == MARCH_LINEAR, step, lam, n2)) {
@@ -768,7 +774,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
           lam *= 0.5;
           ++halv;
           if (++trial <= A.ls_max) continue;
-          status = QE_ERR_LINESEARCH;
+          handed = true;
           break;
         }
         if (step)
@@ -804,14 +810,17 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
       }
       kry += iters;
       if (stage == MARCH_LINEAR) init_kry = iters;
-      step = why == PCG_CONVERGED || why == PCG_MAXIT;
-      if (!step && !(stage == MARCH_LINEAR && A.lenient)) {
-        status = why == PCG_BREAKDOWN ? QE_ERR_KRYLOV_BREAKDOWN : QE_ERR_NONFINITE;
-        break;
-      }
+      handed = why == PCG_BREAKDOWN || why == PCG_NONFINITE;
+      if (handed) break;
+      step = true;
       if (stage == MARCH_LINEAR) stage = MARCH_INITIAL;
       lam = 1.0;
       trial = 0;
+    }
+    if (handed) {   // (every workgroup alike: the sums are the same in all)
+      give_up();
+      __syncthreads();
+      continue;
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q)

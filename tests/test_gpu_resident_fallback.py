@@ -63,3 +63,42 @@ def test_start_is_the_callers_whatever_was_written(monkeypatch, n):
         assert which == 0 or torch.equal(phi, march), k
         seen[which] += 1
     assert seen[1] > 0
+
+
+def thin():
+    """its thin elements put the floor of ||F|| at 1e-11: the line search fails"""
+    return synth.double_dot_device("l", 13, 11, 101, VOLTS)
+
+
+def floating():
+    """no Dirichlet node: J is singular for the charge-free guess, and the CG breaks down"""
+    dev = synth.double_dot_device("l", 17, 17, 9, VOLTS)
+    dev.dir_id[:] = -1
+    return dev
+
+
+@pytest.mark.parametrize("make,status", [(thin, -5), (floating, -6)])
+def test_failure_is_the_marchs(monkeypatch, make, status):
+    """a line search that fails and a CG that breaks down: the status, the
+    report and the last iterate are those of the march, whose CG takes p^T J p
+    directly; so with a warm start, and in the batch (which skips a linear
+    guess that fails)"""
+    P = qe.Problem(make())
+
+    def solves():
+        opts = dict(newton_atol=2e-12, newton_maxit=20)
+        phi, n, rep = qe.qe_solve(P, opts=qe.qe_default_options(**opts), check=False)
+        out = [(phi, n, rep)]
+        if status == -5:
+            out.append(qe.qe_solve(P, opts=qe.qe_default_options(init_guess=1, **opts), phi=0.9 * phi, check=False))
+        phis, _, reps = qe.qe_solve_batch([P, P], opts=qe.qe_default_options(**opts), check=False)
+        return out + [(f, f, rep) for f, rep in zip(phis, reps)]
+
+    got = solves()
+    monkeypatch.setenv("QE_RESIDENT", "0")
+    ref = solves()
+    assert ref[0][2]["status"] == status
+    for (phi, n, rep), (rphi, rn, rrep) in zip(got, ref):
+        assert rep == rrep
+        if rrep["status"] in (-5, -6):
+            assert torch.equal(phi, rphi) and torch.equal(n, rn)
