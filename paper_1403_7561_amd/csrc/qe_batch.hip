@@ -449,7 +449,8 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
            hip_ok(hipMemcpyAsync(res.data(), ws + H.state_b, res.size(), hipMemcpyDeviceToHost, s)) &&
            hip_ok(hipStreamSynchronize(s));
   };
-  if (placed > 0) {
+  ResidentTurn turn(placed > 0);
+  if (turn.held()) {
     ResArgs ra;
     std::memset(&ra, 0, sizeof(ra));
     ra.inst = reinterpret_cast<const ResInst*>(ws + H.res);
@@ -457,6 +458,7 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
     ra.seats = reinterpret_cast<const int2*>(ws + H.seats);
     ra.n_seats = n_seats;
     ra.ticket = a.done + 16;
+    ra.started = a.done + 17;
     ra.abort = reinterpret_cast<unsigned long long*>(a.done + 32);
     ra.ch = ch;
     ra.atol = a.atol;
@@ -469,13 +471,15 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
     ra.apply = ra.zero_free = 1;
     if ((st = launch_resident(s, ra, plans.data(), n_inst, wgs)) != QE_OK) return st;
   }
-  bool all = placed == n_inst;
+  bool all = turn.held() && placed == n_inst;
   if (n_boxes > 0 && all) launch_march_count(s, a, bs, reinterpret_cast<double*>(ws + H.counts));
   if (all) {
     if (!read_back()) return fail(QE_ERR_HIP, "batch kernel failed");
     for (int i = 0; i < n_inst; ++i) all = all && hs[i].phase == MARCH_DONE;
   }
   if (!all) {
+    if (turn.held() && !hip_ok(hipStreamSynchronize(s))) return fail(QE_ERR_HIP, "batch kernel failed");
+    turn.release();   // (the march takes as long as it takes)
     hm.prog->word = 0;
     a.prog = hm.prog_dev;
     launch_march_stage(s, a);

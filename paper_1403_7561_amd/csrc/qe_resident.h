@@ -56,14 +56,32 @@ struct ResArgs {
   int n_inst;
   const int2* seats;         // (instance, box) of every ticket, an instance's boxes in a row
   int n_seats;
-  unsigned int* ticket;      // the next ticket; zeroed by the launch, like abort
+  unsigned int* ticket;      // the next ticket; zeroed by the launch, like started and abort
+  unsigned int* started;     // workgroups that have a compute unit
   unsigned long long* abort; // set when a wait ran out
   Charge ch;
   Quantum qm;                // eigenstates (one instance; n = 0: none)
   double atol, rtol_max, newton_rtol;
   int newton_maxit, ls_max, krylov_maxit;
   int lenient, init, apply, zero_free;
-  int polls_first, polls_later;   // of one wait (set by the launch)
+  int polls_first, polls_later;   // of one wait (set by the launch): while workgroups have not started; at all
+};
+
+// A launch wants every compute unit, and two that each had some would keep each
+// other waiting, so of the calls of this process one at a time runs resident on
+// a device: from the construction, which waits for its turn, until release or
+// the end.  The wait is bounded (the holder's stream may be waiting for the
+// caller's); a call that did not get its turn marches.
+class ResidentTurn {
+  int dev_ = -1;
+
+ public:
+  explicit ResidentTurn(bool wanted);
+  ~ResidentTurn() { release(); }
+  ResidentTurn(const ResidentTurn&) = delete;
+  ResidentTurn& operator=(const ResidentTurn&) = delete;
+  bool held() const { return dev_ >= 0; }
+  void release();
 };
 
 // Boxes whose part fits `bytes`, at most wgs.

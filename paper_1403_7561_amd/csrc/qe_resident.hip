@@ -33,9 +33,10 @@
 // can run, whatever the boxes' numbers.
 //
 // Waiting: an instance needs all its workgroups at once.  A launch has at most
-// one per compute unit, so on a device without other work they all run; when
-// other work keeps some out for too long, every wait ends after a bounded
-// number of polls, the workgroups leave, the instance's state says that it is
+// one per compute unit, so on a device without other work they all run (this
+// process's launches take turns: ResidentTurn); when other work keeps some out
+// for too long, every wait ends after a bounded number of polls, much fewer
+// while some have not started; then the workgroups leave, the instance's state says that it is
 // not finished, and the host takes the tick-by-tick march instead, from the
 // caller's phi: workgroups that had the last exchange in time have written
 // their part by then, so a warm start is kept and put back.
@@ -47,6 +48,8 @@
 // boxes takes ~6 us: product and updates 1.9, sums of the workgroup 0.9,
 // publishing 0.5, waiting 2.6, sums of all 0.5.
 #include <algorithm>
+#include <chrono>
+#include <mutex>
 #include <vector>
 
 #include "qe_resident.h"
@@ -54,9 +57,11 @@
 
 namespace qe {
 
-// Polls of one wait (each a round trip to memory, ~0.5 us or more): the first
-// wait of a single instance, when workgroups may still be waiting for a compute
-// unit, and the others.  QE_RESIDENT_POLLS sets both (tests of the fallback).
+// Polls of one wait (each a round trip to memory, ~0.5 us or more): an
+// instance's first while some workgroups of the launch still have no compute
+// unit, and any.  (With all of them running, the first wait of one of several
+// instances may last as long as other instances' solves.)  QE_RESIDENT_POLLS
+// sets both (tests of the fallback).
 constexpr int kResPollsFirst = 20000, kResPollsLater = 2000000;
 
 // MarchState::phase of an instance that is not finished: one of its workgroups
@@ -66,6 +71,9 @@ constexpr int kResGaveUp = -1;
 typedef unsigned long long res_word;
 
 __device__ __forceinline__ res_word agent_load(const res_word* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned int agent_load(const unsigned int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void agent_store(res_word* p, res_word v) {
@@ -147,6 +155,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
   // may set it at any time, and waves that read it apart could part ways.
   if (t == 0) {
     s_dead = agent_load(A.abort) != 0u ? 1 : 0;
+    __hip_atomic_fetch_add(A.started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_ch = A.ch;
     if constexpr (kQ) s_qm = A.qm;
   }
@@ -158,7 +167,9 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
   auto waited = [&](bool here, int& k) -> bool {
     if (__builtin_amdgcn_ballot_w64(!here) == 0) return true;
     ++k;
-    if (k >= ((kOne && epoch <= 1u) ? A.polls_first : A.polls_later) || ((k & 255) == 255 && agent_load(A.abort) != 0u)) {
+    if (k >= A.polls_later ||
+        ((k & 255) == 255 &&
+         (agent_load(A.abort) != 0u || (epoch <= 1u && k >= A.polls_first && agent_load(A.started) < gridDim.x)))) {
       agent_store(A.abort, 1u);
       s_dead = 1;
       return true;
@@ -856,6 +867,24 @@ int resident_wgs() {
   return std::min(cus, kResMaxWgs);
 }
 
+// As long as several single solves; a launch's first wait is no shorter.
+constexpr std::chrono::milliseconds kResTurn(20);
+constexpr int kResDevices = 64;
+static std::timed_mutex& resident_mutex(int dev) {
+  static std::timed_mutex m[kResDevices];
+  return m[dev];
+}
+ResidentTurn::ResidentTurn(bool wanted) {
+  int dev = -1;
+  if (wanted && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kResDevices &&
+      resident_mutex(dev).try_lock_for(kResTurn))
+    dev_ = dev;
+}
+void ResidentTurn::release() {
+  if (dev_ >= 0) resident_mutex(dev_).unlock();
+  dev_ = -1;
+}
+
 static size_t resident_lds(const ResPlan& p) {
   const size_t nel = (size_t)(p.tx + 1) * (p.ty + 1) * (p.tz + 1);
   const size_t planes = 2 * ((p.tz + 1) / 2) + 2;
@@ -915,11 +944,12 @@ int resident_fit(size_t bytes, long nodes, int wgs) {
 }
 
 // Zeroes the buffers between the boxes of every instance (w0, w1 and d are
-// six vectors that follow each other; then the part) and the launch's two
+// six vectors that follow each other; then the part) and the launch's
 // counters, sets the state's phase, and keeps phi where that is asked for.
 __global__ __launch_bounds__(256) void k_resident_zero(ResArgs A) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     *A.ticket = 0u;
+    *A.started = 0u;
     *A.abort = 0ull;
   }
   for (int k = blockIdx.y; k < A.n_inst; k += gridDim.y) {

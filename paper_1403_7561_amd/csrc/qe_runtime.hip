@@ -648,6 +648,7 @@ ResArgs Context::resident_args(const MarchArgs& a, const ResPlan& plan, const in
   I.part = reinterpret_cast<unsigned long long*>(ws + lay.c);
   R.n_inst = 1;
   R.ticket = u32(lay.counters) + 9;
+  R.started = u32(lay.counters) + 10;
   R.abort = reinterpret_cast<unsigned long long*>(ws + lay.flags) + 1;
   R.ch = a.ch;
   R.qm = quantum;
@@ -1400,7 +1401,8 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
     ResPlan plan;
     // (what the boxes exchange fits the coefficients' room)
     const int wgs = resident_fit((size_t)cx.nslots * 64, cx.N, resident_wgs());
-    if (resident_on() && resident_plan(p->nx, p->ny, p->nz, wgs, false, plan)) {
+    ResidentTurn turn(resident_on() && resident_plan(p->nx, p->ny, p->nz, wgs, false, plan));
+    if (turn.held()) {
       ResArgs ra = cx.resident_args(a, plan, flags);
       if ((st = launch_resident(cx.s, ra, &plan, 1, wgs)) != QE_OK) return finish(st, r, rep);
       if (!result()) return finish(fail(QE_ERR_HIP, "stream error at the end of the solve"), r, rep);
@@ -1409,6 +1411,7 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       if (S.phase != MARCH_DONE && ra.one.keep &&
           hipMemcpyAsync(phi, ra.one.keep, cx.N * sizeof(double), hipMemcpyDeviceToDevice, cx.s) != hipSuccess)
         return finish(fail(QE_ERR_HIP, "copy of the initial potential failed"), r, rep);
+      turn.release();
     }
     if (S.phase != MARCH_DONE && march) {
       a.flags = const_cast<int*>(flags);
