@@ -269,6 +269,7 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
                          double* const* phi, int32_t n_boxes, const double* boxes, double* counts,
                          const char* tune_cache, void* ws_, size_t ws_bytes, void* stream, qe_report* reps) {
   clear_error();
+  clear_routes();
   if (n_inst < 1 || !probs || !phi) return fail(QE_ERR_INVALID_ARG, "need n_inst >= 1, probs and phi");
   qe_status st;
   if ((st = check_options(o)) != QE_OK) return st;
@@ -471,6 +472,7 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
     ra.apply = ra.zero_free = 1;
     if ((st = launch_resident(s, ra, plans.data(), n_inst, wgs)) != QE_OK) return st;
   }
+  const bool tried = turn.held();
   bool all = turn.held() && placed == n_inst;
   if (n_boxes > 0 && all) launch_march_count(s, a, bs, reinterpret_cast<double*>(ws + H.counts));
   if (all) {
@@ -504,6 +506,7 @@ qe_status qe_solve_batch(int32_t n_inst, const qe_problem* probs, const qe_physi
       r.res_final = hs[i].nrm;
     }
     for (int b = 0; b < n_boxes; ++b) counts[(long)i * n_boxes + b] = hc[(long)i * n_boxes + b];
+    add_route(hs[i].resident ? ROUTE_RESIDENT : tried && plans[i].nwg > 0 ? ROUTE_LEFT : ROUTE_OTHER);
     if (hs[i].status != QE_OK && worst == QE_OK) worst = (qe_status)hs[i].status;
   }
   if (worst != QE_OK) return fail(worst, "at least one instance did not converge (see the reports)");

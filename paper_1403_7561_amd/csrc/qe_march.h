@@ -27,6 +27,7 @@ struct MarchState {
   int step;        // x + alpha p (x alone before the first iteration) is the current CG solution
   int iters;       // iterations of the current CG solve
   int newton, trial, kry, init_kry, halv, nres;
+  int resident;    // 1: finished by the resident solve
   double rz, alpha, tol2, rtol, lam, nrm, res0;
 };
 

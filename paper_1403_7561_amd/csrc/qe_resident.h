@@ -84,6 +84,13 @@ class ResidentTurn {
   void release();
 };
 
+// How the solves of this thread's last call went, in their order (a coarse start
+// before the solve that it starts; a batch's instances), for the tests:
+// qe_last_routes copies up to n of them and returns their number.
+enum SolveRoute : uint8_t { ROUTE_OTHER = 0, ROUTE_RESIDENT = 1, ROUTE_LEFT = 2 };   // LEFT: tried resident, solved otherwise
+void clear_routes();
+void add_route(SolveRoute r);
+
 // Boxes whose part fits `bytes`, at most wgs.
 int resident_fit(size_t bytes, long nodes, int wgs);
 // Zeroes the exchange buffers, then solves on at most wgs workgroups (a single

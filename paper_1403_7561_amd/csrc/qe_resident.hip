@@ -848,6 +848,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
       S->init_kry = init_kry;
       S->halv = halv;
       S->nres = nres;
+      S->resident = 1;
       S->nrm = nrm;
       S->res0 = res0;
       int expected = MARCH_RES;
@@ -865,6 +866,14 @@ int resident_wgs() {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
   return std::min(cus, kResMaxWgs);
+}
+
+constexpr int kMaxRoutes = 4096;
+static thread_local uint8_t t_routes[kMaxRoutes];
+static thread_local int t_n_routes = 0;
+void clear_routes() { t_n_routes = 0; }
+void add_route(SolveRoute r) {
+  if (t_n_routes < kMaxRoutes) t_routes[t_n_routes++] = r;
 }
 
 // As long as several single solves; a launch's first wait is no shorter.
@@ -993,3 +1002,8 @@ qe_status launch_resident(hipStream_t s, ResArgs a, const ResPlan* plans, int n_
 }
 
 }  // namespace qe
+
+extern "C" int qe_last_routes(uint8_t* out, int n) {
+  for (int i = 0; i < std::min(n, qe::t_n_routes); ++i) out[i] = qe::t_routes[i];
+  return qe::t_n_routes;
+}

@@ -1401,6 +1401,7 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
     ResPlan plan;
     // (what the boxes exchange fits the coefficients' room)
     const int wgs = resident_fit((size_t)cx.nslots * 64, cx.N, resident_wgs());
+    SolveRoute route = ROUTE_OTHER;
     ResidentTurn turn(resident_on() && resident_plan(p->nx, p->ny, p->nz, wgs, false, plan));
     if (turn.held()) {
       ResArgs ra = cx.resident_args(a, plan, flags);
@@ -1412,7 +1413,9 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
           hipMemcpyAsync(phi, ra.one.keep, cx.N * sizeof(double), hipMemcpyDeviceToDevice, cx.s) != hipSuccess)
         return finish(fail(QE_ERR_HIP, "copy of the initial potential failed"), r, rep);
       turn.release();
+      route = S.phase == MARCH_DONE ? ROUTE_RESIDENT : ROUTE_LEFT;
     }
+    add_route(route);
     if (S.phase != MARCH_DONE && march) {
       a.flags = const_cast<int*>(flags);
       if (hm.prog) hm.prog->word = 0;
@@ -1452,6 +1455,7 @@ static qe_status solve_impl(const qe_problem* p, const qe_physics* ph, const qe_
       return finish(st, r, rep);
     }
   }
+  if (!march && !states) add_route(ROUTE_OTHER);
   if ((st = cx.stage(phi, 1, linear ? 1 : 0)) != QE_OK) return finish(st, r, rep);
   if (mixed) {
     launch_stage_eps32(cx.s, cx.vblocks, cx.g, p->eps_r, cx.f32(cx.lay.eps32), cx.nslots);
@@ -1612,12 +1616,14 @@ extern "C" {
 
 qe_status qe_solve(const qe_problem* p, const qe_physics* ph, const qe_options* o, double* phi, double* n_nodal,
                    void* ws, size_t ws_bytes, void* stream, qe_report* rep) {
+  clear_routes();
   return solve_impl(p, ph, o, phi, n_nodal, ws, ws_bytes, stream, rep, false);
 }
 
 qe_status qe_solve_static(const qe_problem* p, const qe_physics* ph, const qe_options* o, double* phi,
                           double* n_nodal, void* stream, qe_report* rep) {
   clear_error();
+  clear_routes();
   qe_report r;
   std::memset(&r, 0, sizeof(r));
   qe_status st;
