@@ -37,6 +37,9 @@
  *  - `ws` is caller-owned device scratch of at least qe_workspace_bytes()
  *    bytes, 256-byte aligned; its contents on entry are irrelevant and on
  *    return unspecified.  Concurrent calls must not share a workspace.
+ *    (Solves that run on all compute units at once take turns on a device;
+ *    one that waits 20 ms for its turn takes another path to the same
+ *    solution, whose last bits may differ.)
  *  - `stream` is a hipStream_t passed as void* (NULL = default stream).  All
  *    device work is enqueued on it; every entry point returns after
  *    synchronising that stream.
@@ -268,8 +271,8 @@ size_t qe_workspace_bytes(const qe_problem* p, const qe_options* o);
  * coarse element takes the materials of its first fine element), that
  * problem is solved from the linear guess until ||F|| falls to a fraction
  * 1e-3 (139425 / N_coarse)^(1/3) of its initial value (a finer coarse mesh
- * is worth solving further; measured; its CG runs in FP32 inside its FP64
- * Newton, as in mixed precision), and its potential, interpolated
+ * is worth solving further; measured; on a coarse mesh of 250000 nodes or
+ * more its CG runs in FP32 inside its FP64 Newton, as in mixed precision), and its potential, interpolated
  * trilinearly, starts Newton here; the solution is the same (the discrete problem has one
  * solution), only the iteration counts change.  Smaller meshes, sheets,
  * eigenstates, a coarse solve that fails, or a workspace without room for

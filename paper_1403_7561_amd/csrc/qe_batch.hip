@@ -1,7 +1,7 @@
 // Batched solve of many independent devices (a gate-voltage sweep over
 // uneven meshes).  Instances that fit are solved resident on the chip
 // (qe_resident.h), as many at a time as their boxes fit the compute units.
-// The others, and any whose launch could not get the chip to itself, march
+// The others, and any that its workgroups left unfinished, march
 // together (qe_march.h): every launch advances all of them, so their number
 // bounds nothing but the traffic.
 //

@@ -36,14 +36,14 @@
 // one per compute unit, so on a device without other work they all run (this
 // process's launches take turns: ResidentTurn); when other work keeps some out
 // for too long, every wait ends after a bounded number of polls, much fewer
-// while some have not started; then the workgroups leave, the instance's state says that it is
-// not finished, and the host takes the tick-by-tick march instead, from the
-// caller's phi: workgroups that had the last exchange in time have written
-// their part by then, so a warm start is kept and put back.
+// while some have not started; then the workgroups leave, the instance's state
+// says that it is not finished, and the host takes the tick-by-tick march
+// instead, from the caller's phi: workgroups that had the last exchange in time
+// have written their part by then, so a warm start is kept and put back.
 //
 // Measured, whole solves, with the host-driven launches of one kernel per CG
 // step / the march / resident: 17x17x9 3.2 / 2.5 / 0.85 ms, a junction of
-// 33x29x41 10.9 / 10.7 / 3.3, 65x65x33 7.2 / 6.4 / 3.1; 256 instances of 33x33x17
+// 33x29x41 11.7 / 10.7 / 3.4, 65x65x33 7.4 / 6.4 / 3.3; 256 instances of 33x33x17
 // to 65x65x33 in one call 505 / 251 / 245.  A CG iteration at 65x65x33 in 169
 // boxes takes ~6 us: product and updates 1.9, sums of the workgroup 0.9,
 // publishing 0.5, waiting 2.6, sums of all 0.5.
@@ -135,7 +135,7 @@ __device__ __attribute__((noinline)) ResCharge res_charge_n(const Charge* ch, do
 
 // kQ: electrons from eigenstates (one instance), summed per element like the
 // wave-tiled residual's (pc_states).  65x65x33 nodes with 16 states: 406 CG
-// iterations and 12 residuals in 4.6 ms, against 8.6 with host-driven launches.
+// iterations and 12 residuals in 4.1 ms, against 8.4 with host-driven launches.
 template <bool kOne, bool kQ>
 __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs A) {
   extern __shared__ double lds[];
